@@ -820,6 +820,7 @@ struct RunOut {
   // cache (no allocation, no profiling events): the no-allocation entry point.
   void *ext_base = nullptr;
   size_t ext_bytes = 0;
+  bool pack = false;  // NodeArgs::pack
 };
 
 int run(gnn_handle *hd, const float *x, const int32_t *ei, int64_t N, int64_t E,
@@ -910,6 +911,7 @@ int run(gnn_handle *hd, const float *x, const int32_t *ei, int64_t N, int64_t E,
     na.nchunks = fd.enc_chunks;
     na.s2 = fd.s2_ne;
     na.nproj = 2;
+    na.pack = ro.pack;
     // with no iteration h0 feeds the classifier only through pb
     na.h_out = T == 0 && ro.stop_iter < 0 ? nullptr : (float *)w.h;
     na.p_out[0] = w.pa;
@@ -953,6 +955,7 @@ int run(gnn_handle *hd, const float *x, const int32_t *ei, int64_t N, int64_t E,
       ea.g2 = m.l1.g;
       ea.beta2 = m.l1.beta;
       ea.eps = d.ln_eps;
+      ea.pack = ro.pack;
       return ea;
     };
     auto launch_edge = [&](EdgeMode mode, const EdgeArgs &ea, int grid) {
@@ -1033,6 +1036,7 @@ int run(gnn_handle *hd, const float *x, const int32_t *ei, int64_t N, int64_t E,
         nu.row_bound = fd.row_bound;
       }
       nu.nproj = 1;
+      nu.pack = ro.pack;
       // In place: a wave reads its rows before writing them.  The last
       // update's h reaches the classifier only through its projections, so
       // it is not stored unless the stages are being exported.
@@ -1200,6 +1204,16 @@ namespace gnn {
 StageEvents &stage_events() {
   static thread_local StageEvents ev;
   return ev;
+}
+
+int infer_shared(gnn_handle *h, const float *node_feat, const int32_t *edge_index, int64_t n_nodes,
+                 int64_t n_edges, float *edge_scores, hipStream_t stream) {
+  const int rc = common_checks(h, node_feat, edge_index, n_nodes, n_edges, edge_scores);
+  if (rc || n_edges == 0) return rc;
+  RunOut ro;
+  ro.scores = edge_scores;
+  ro.pack = true;
+  return run(h, node_feat, edge_index, n_nodes, n_edges, stream, ro);
 }
 
 // Detaches the handle's cached workspaces from `stream` before the caller

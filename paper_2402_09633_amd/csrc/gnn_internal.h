@@ -122,6 +122,9 @@ struct NodeArgs {
   // P[v][0:H] as the rows are stored, so the edge kernels add none
   const float *pbias[2] = {nullptr, nullptr};
   float ps1[2] = {1.f, 1.f};
+  // split kernels, host side: other calls are expected to run on the GPU at
+  // the same time, so a small launch takes as few CUs as it can
+  bool pack = false;
 };
 
 // UpdAgg: the edge update that also sums its output rows per source node
@@ -148,6 +151,7 @@ struct EdgeArgs {
   // split kernels: power-of-two scales of the first layer (W_e and the
   // stored P rows) and of W2
   float s1 = 1.f, s2 = 1.f;
+  bool pack = false;  // split kernels, host side: as in NodeArgs
   // UpdAgg: the sum of every run of rows with one source node that lies
   // inside one 32-row unit goes to agg_out[src] (row type); a run cut by a
   // unit boundary leaves its piece in agg_part[unit][0] (the unit's first
@@ -316,6 +320,10 @@ hipError_t launch_bf16_to_f32(const void *in, float *out, int64_t n, hipStream_t
 // Detaches a handle's cached workspaces from a stream about to be destroyed
 // (host; the stream's work must have finished).
 void ws_forget_stream(gnn_handle *h, hipStream_t stream);
+
+// gnn_infer for one of several calls that share the GPU (NodeArgs::pack).
+int infer_shared(gnn_handle *h, const float *node_feat, const int32_t *edge_index, int64_t n_nodes,
+                 int64_t n_edges, float *edge_scores, hipStream_t stream);
 
 // Sets the calling thread's gnn_last_error() text; returns code (host).
 int set_error(int code, const char *msg);

@@ -58,6 +58,7 @@ struct gnn_server {
   bool stopping = false;
   int start_errors = 0;
   hipEvent_t t0 = nullptr;  // time origin of the device intervals
+  bool shared = false;      // several instances share the GPU
 };
 
 namespace {
@@ -92,7 +93,8 @@ void worker(gnn_server *s) {
     // (the events are reused: the previous request's work has finished)
     const bool timed = hipEventRecord(ev[0], stream) == hipSuccess;
     if (!timed) (void)hipGetLastError();
-    int rc = gnn_infer(s->model, r.x, r.ei, r.n_nodes, r.n_edges, r.out, stream);
+    int rc = s->shared ? gnn::infer_shared(s->model, r.x, r.ei, r.n_nodes, r.n_edges, r.out, stream)
+                       : gnn_infer(s->model, r.x, r.ei, r.n_nodes, r.n_edges, r.out, stream);
     const bool timed_end = timed && hipEventRecord(ev[1], stream) == hipSuccess;
     std::string err;
     if (rc == GNN_OK) {
@@ -181,6 +183,7 @@ gnn_server *gnn_server_create(gnn_handle *h, int n_instances) {
     gnn::set_error(GNN_E_HIP, "creating the server's time-origin event failed");
     return nullptr;
   }
+  s->shared = n_instances > 1;
   for (int i = 0; i < n_instances; ++i) s->workers.emplace_back(worker, s);
   return s;
 }

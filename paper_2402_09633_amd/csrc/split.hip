@@ -1004,9 +1004,22 @@ __global__ __launch_bounds__((64 * edge_waves<PREC, MODE>())) void edge_split(Ed
 
 template <int MB, int PREC>
 hipError_t node_h(bool enc, const NodeArgs &a, int grid, hipStream_t stream) {
-  const int64_t tiles = (a.n_rows + 32 * SW - 1) / (32 * SW);
-  if (tiles <= 0) return hipSuccess;
-  const unsigned nb = (unsigned)(tiles < grid ? tiles : grid);
+  const int64_t units = (a.n_rows + 31) / 32;
+  if (units <= 0) return hipSuccess;
+  // Workgroups of a launch with less than one full round.  A unit keeps one
+  // wave busy for tens of microseconds, so up to four units per CU they are
+  // spread one per workgroup before any workgroup takes a second (8 waves of
+  // one CU would share its four SIMDs while other CUs idle).  H = 128, T = 8,
+  // fp32, us per event, packed 8 to a workgroup -> spread: 2k hits 598 -> 484,
+  // 10k 651 -> 545, 30k 979 -> 904; bf16 10k 513 -> 459, 30k 717 -> 685.
+  // Above that the waves fill the CUs either way and every further workgroup
+  // streams the weights once more: 50k hits 1698 packed, 1740 spread.  When
+  // several calls share the chip (a.pack) the idle CUs belong to the other
+  // calls, and packing is better: 4 queued events of 30k hits 1665 packed,
+  // 1770 spread.
+  const bool spread = !a.pack && units <= 4 * (int64_t)grid;
+  const int64_t wgs = spread ? units : (units + SW - 1) / SW;
+  const unsigned nb = (unsigned)(wgs < grid ? wgs : grid);
   if (!enc) return launch(node_split<MB, false, 1, PREC>, nb, 64 * SW, 0, stream, a);
   if (a.nproj == 2) return launch(node_split<MB, true, 2, PREC>, nb, 64 * SW, 0, stream, a);
   return launch(node_split<MB, true, 1, PREC>, nb, 64 * SW, 0, stream, a);
@@ -1016,9 +1029,14 @@ template <int MB, int PREC, int MODE>
 hipError_t edge_go(const EdgeArgs &a, int grid, hipStream_t stream) {
   constexpr int EW = edge_waves<PREC, MODE>();
   const int64_t units = (a.n_rows + 31) / 32;
-  const int64_t need = (units + EW - 1) / EW;
-  if (need <= 0) return hipSuccess;
-  const unsigned nb = (unsigned)(need < grid ? need : grid);
+  if (units <= 0) return hipSuccess;
+  // One unit per workgroup before any workgroup takes a second (unit_at):
+  // the waves of a small event run on SIMDs of their own.  T = 8, H = 128,
+  // us per event against packed workgroups: 2k hits fp32 597 -> 514, 10k
+  // 651 -> 637, bf16 10k 513 -> 497; no change from 20k hits on.  Not with
+  // a.pack: 4 queued events of 30k hits 1651 packed, 1669 spread.
+  const int64_t wgs = a.pack ? (units + EW - 1) / EW : units;
+  const unsigned nb = (unsigned)(wgs < grid ? wgs : grid);
   return launch(edge_split<MB, MODE, PREC>, nb, 64 * EW, 0, stream, a);
 }
 

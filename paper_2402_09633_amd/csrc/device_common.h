@@ -103,12 +103,15 @@ __device__ __forceinline__ void bias_ln_relu(f16v (&acc)[MB], const float *__res
 // LayerNorm epilogue with its parameters (b, gamma, beta; H floats each)
 // read from LDS (the bias already multiplied by the accumulators' scale,
 // eps by its square).  ADD_BIAS false: the bias is in the accumulators
-// already (b is then not read).
-template <int MB, bool ADD_BIAS = true>
+// already (b is then not read).  CENTERED: the layer's weights and bias had
+// their mean over the output features taken out when the handle was made
+// (centred() in gnn_api.hip), so the rows have mean zero but for rounding
+// and no mean is formed.
+template <int MB, bool ADD_BIAS = true, bool CENTERED = false>
 __device__ __forceinline__ void ln_relu_lds(f16v (&acc)[MB], const float *prm, float eps, int hh) {
   constexpr int H = 32 * MB;
   constexpr float inv_h = 1.0f / H;
-  float s = 0.f;
+  float s = 0.f, mean = 0.f;
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -118,11 +121,13 @@ __device__ __forceinline__ void ln_relu_lds(f16v (&acc)[MB], const float *prm, f
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         if constexpr (ADD_BIAS) acc[mb][4 * q + t] += bb[t];
-        s += acc[mb][4 * q + t];
+        if constexpr (!CENTERED) s += acc[mb][4 * q + t];
       }
     }
-  s += __shfl_xor(s, 32);
-  const float mean = s * inv_h;
+  if constexpr (!CENTERED) {
+    s += __shfl_xor(s, 32);
+    mean = s * inv_h;
+  }
   // centred in place: the normalisation reuses x - mean (same roundings as
   // recomputing it, one subtraction fewer per value)
   float var = 0.f;
@@ -130,7 +135,7 @@ __device__ __forceinline__ void ln_relu_lds(f16v (&acc)[MB], const float *prm, f
   for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      acc[mb][v] -= mean;
+      if constexpr (!CENTERED) acc[mb][v] -= mean;
       var += acc[mb][v] * acc[mb][v];
     }
   var += __shfl_xor(var, 32);

@@ -19,6 +19,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <deque>
 #include <vector>
 
 #include "../../include/gnn.h"
@@ -160,7 +161,8 @@ uint16_t f16_bits(_Float16 v) {
 
 // Power of two s with max |s W| in [2^13, 2^14) (1 for an all-zero or
 // non-finite W), over the whole (fout x fin) layer.
-float pow2_scale(const BlobLayer &L) {
+constexpr int MIN_SCALE = -40;  // (centred weights: two more, centred())
+float pow2_scale(const BlobLayer &L, int kmin = MIN_SCALE) {
   float mx = 0.f;
   const size_t n = (size_t)L.fout * L.fin;
   for (size_t i = 0; i < n; ++i) mx = fmaxf(mx, fabsf(L.W[i]));
@@ -168,9 +170,34 @@ float pow2_scale(const BlobLayer &L) {
   int e = 0;
   (void)frexpf(mx, &e);  // mx = m 2^e, m in [0.5, 1)
   int k = 14 - e;
-  k = k < -40 ? -40 : (k > 40 ? 40 : k);
+  k = k < kmin ? kmin : (k > 40 ? 40 : k);
   return ldexpf(1.f, k);
 }
+
+// L with the mean over its output features taken out of every weight column
+// and of the bias.  The LayerNorm that follows subtracts exactly that mean
+// from each row (mean_f (W x + b)_f = (mean_f W_f) x + mean_f b_f), so its
+// result is the same, and the kernel need not form the mean: per row and
+// LayerNorm two operations per feature and one cross-lane reduction fewer.
+// The column means are formed in double and the differences rounded once to
+// fp32, below the rounding of the products that follow.  |W'| <= 2 |W|, one
+// bit more than the limits checked on W itself.
+struct Centred {
+  std::vector<float> W, b;
+  BlobLayer L;
+  explicit Centred(const BlobLayer &src) : W((size_t)src.fin * src.fout), b(src.fout), L(src) {
+    for (int k = 0; k <= src.fin; ++k) {
+      auto at = [&](int f) { return k < src.fin ? src.W[(size_t)f * src.fin + k] : src.b[f]; };
+      double m = 0.0;
+      for (int f = 0; f < src.fout; ++f) m += (double)at(f);
+      m /= src.fout;
+      for (int f = 0; f < src.fout; ++f)
+        (k < src.fin ? W[(size_t)f * src.fin + k] : b[f]) = (float)((double)at(f) - m);
+    }
+    L.W = W.data();
+    L.b = b.data();
+  }
+};
 
 // Largest value a LayerNorm/ReLU output of layer L can take:
 // |(y - mean) / sqrt(var + eps)| <= sqrt(H - 1) for every feature.
@@ -259,8 +286,8 @@ std::vector<uint16_t> rec_bf16x2(const BlobLayer &L, int c0, int K, int grp, flo
 // bf16 model: power of two s for the fp16 projections s P = s [W_s h; W_d h]
 // that edge-side layer L reads (columns [0, H) and [H, 2H) of its W), with
 // s max_f sum_k |W[f][k]| hb <= 2^15 for an h bound hb, as large as that
-// allows within [2^-40, 2^40]; 0 if none fits.
-float proj_f16_scale(const BlobLayer &L, int H, double hb) {
+// allows within [2^kmin, 2^40]; 0 if none fits.
+float proj_f16_scale(const BlobLayer &L, int H, double hb, int kmin = MIN_SCALE) {
   double m = 0.0;
   for (int f = 0; f < L.fout; ++f)
     for (int half = 0; half < 2; ++half) {
@@ -274,7 +301,7 @@ float proj_f16_scale(const BlobLayer &L, int H, double hb) {
   int e = 0;
   (void)frexp(32768.0 / bound, &e);  // 2^(e-1) <= 2^15 / bound < 2^e
   int k = e - 1;
-  k = k < -40 ? -40 : (k > 40 ? 40 : k);
+  k = k < kmin ? kmin : (k > 40 ? 40 : k);
   const double sc = ldexp(1.0, k);
   return sc * bound <= 32768.0 ? (float)sc : 0.f;
 }
@@ -1313,43 +1340,30 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
   size_t o_we_cls = 0, o_enc_stream = 0, o_w2_ee = 0, o_we_em0_acc = 0;
   std::vector<size_t> o_we_em(S), o_upd_stream(T), o_w2_em(S);
   bool split = false;
+  std::deque<Centred> centred;  // storage of the centred layers (split kernels)
   FactDev fdh;  // scales of the split path (pointers are fixed up below)
   {
     BlobLayer a0 = next(F, H, true), a1 = next(H, H, true);
-    o_ne = {stage_layer(st, a0, WKind::PlainT, bf16, true),
-            stage_layer(st, a1, WKind::FragAcc, bf16, true)};
     BlobLayer b0 = next(2 * H, H, true), b1 = next(H, H, true);
-    o_ee = {stage_layer(st, b0, WKind::FragMem, bf16, true),
-            stage_layer(st, b1, WKind::FragAcc, bf16, true)};
     std::vector<BlobLayer> e0s, e1s, n0s, n1s;
     for (int s = 0; s < S; ++s) {
-      BlobLayer e0 = next(3 * H, H, true), e1 = next(H, H, true);
-      o_em[s] = {stage_layer(st, e0, WKind::FragMem, bf16, true),
-                 stage_layer(st, e1, WKind::FragAcc, bf16, true)};
-      BlobLayer n0 = next(3 * H, H, true), n1 = next(H, H, true);
-      o_nm[s] = {stage_layer(st, n0, WKind::FragMem, bf16, true),
-                 stage_layer(st, n1, WKind::FragAcc, bf16, true)};
-      e0s.push_back(e0);
-      e1s.push_back(e1);
-      n0s.push_back(n0);
-      n1s.push_back(n1);
+      e0s.push_back(next(3 * H, H, true));
+      e1s.push_back(next(H, H, true));
+      n0s.push_back(next(3 * H, H, true));
+      n1s.push_back(next(H, H, true));
     }
     BlobLayer c0 = next(3 * H, H, true), c1 = next(H, 1, false);
-    o_cls = {stage_layer(st, c0, WKind::FragMem, bf16, true),
-             stage_layer(st, c1, WKind::Plain, bf16, false)};
-    // The edge consumer of the projections computed after node update t
-    // (t = -1: the node encoder's second projection).
-    auto next_edge_l1 = [&](int t) -> const BlobLayer & {
-      return t + 1 < T ? e0s[S == 1 ? 0 : t + 1] : c0;
-    };
+    // Largest LayerNorm output of the hidden layers that feed a product.
+    double bound = 0.0;
+    for (const BlobLayer *L : {&a0, &a1, &b0, &b1}) bound = fmax(bound, ln_out_bound(*L));
+    for (int s = 0; s < S; ++s)
+      for (const BlobLayer *L : {&e0s[s], &e1s[s], &n0s[s], &n1s[s]})
+        bound = fmax(bound, ln_out_bound(*L));
+    double hb = ln_out_bound(a1);  // of the h rows
+    for (int s = 0; s < S; ++s) hb = fmax(hb, ln_out_bound(n1s[s]));
     if (factored && !bf16) {
       // Split products need every LayerNorm output that feeds an f16x2
       // product inside the fp16 range (with a factor 2 to spare).
-      double bound = 0.0;
-      for (const BlobLayer *L : {&a0, &a1, &b0, &b1}) bound = fmax(bound, ln_out_bound(*L));
-      for (int s = 0; s < S; ++s)
-        for (const BlobLayer *L : {&e0s[s], &e1s[s], &n0s[s], &n1s[s]})
-          bound = fmax(bound, ln_out_bound(*L));
       split = !(d.flags & GNN_FP32_MFMA) && bound <= 32768.0;
       fdh.row_bound = (float)bound;
     }
@@ -1363,11 +1377,6 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
         // fp16 operands: every LayerNorm output that feeds a product must
         // lie inside the fp16 range (as for the split products), and the
         // node update scales aggregate rows by the message-row bound
-        double bound = 0.0;
-        for (const BlobLayer *L : {&a0, &a1, &b0, &b1}) bound = fmax(bound, ln_out_bound(*L));
-        for (int s = 0; s < S; ++s)
-          for (const BlobLayer *L : {&e0s[s], &e1s[s], &n0s[s], &n1s[s]})
-            bound = fmax(bound, ln_out_bound(*L));
         if (!(bound <= 32768.0)) {
           fail(GNN_E_UNSUPPORTED,
                "GNN_F16_WEIGHTS: a LayerNorm output bound %g exceeds the fp16 range", bound);
@@ -1375,21 +1384,76 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
         }
         fdh.row_bound = (float)bound;
       }
-      double hb = ln_out_bound(a1);
-      for (int s = 0; s < S; ++s) hb = fmax(hb, ln_out_bound(n1s[s]));
-      fdh.s1_ee = proj_f16_scale(b0, H, hb);
-      fdh.s1_cls = proj_f16_scale(c0, H, hb);
-      bool fits = fdh.s1_ee > 0.f && fdh.s1_cls > 0.f;
+      // Refused weights: no projection scale, or (fp16 weights) a scaled
+      // weight outside the fp16 range.
+      bool fits = true, f16_fits = true;
+      auto check = [&](const BlobLayer &L, int K, float sc) {
+        for (int f = 0; f < L.fout; ++f)
+          for (int k = 0; k < K; ++k)
+            if (!(fabsf(sc * L.W[(size_t)f * L.fin + k]) <= 65504.f)) f16_fits = false;
+      };
+      std::vector<const BlobLayer *> proj_of{&b0, &c0}, dense{&a1, &b1};
       for (int s = 0; s < S; ++s) {
-        fdh.s1_em.push_back(proj_f16_scale(e0s[s], H, hb));
-        fits = fits && fdh.s1_em[s] > 0.f;
+        proj_of.push_back(&e0s[s]);
+        dense.push_back(&e1s[s]);
+        if (T > 0) dense.insert(dense.end(), {&n0s[s], &n1s[s]});
       }
+      for (const BlobLayer *L : proj_of) {
+        const float sc = proj_f16_scale(*L, H, hb);
+        fits = fits && sc > 0.f;
+        check(*L, L->fin, sc);
+      }
+      for (const BlobLayer *L : dense) check(*L, L->fin, pow2_scale(*L));
       if (!fits) {
         fail(GNN_E_UNSUPPORTED,
              "bf16 model: no power-of-two scale keeps these weights' node projections inside "
              "the fp16 range");
         return nullptr;
       }
+      if (f16w && !f16_fits) {
+        fail(GNN_E_UNSUPPORTED, "GNN_F16_WEIGHTS: a scaled weight exceeds the fp16 range");
+        return nullptr;
+      }
+    }
+    if (split) {
+      auto centre = [&](BlobLayer &L) {
+        centred.emplace_back(L);
+        L = centred.back().L;
+      };
+      for (BlobLayer *L : {&a0, &a1, &b0, &b1, &c0}) centre(*L);
+      for (int s = 0; s < S; ++s)
+        for (BlobLayer *L : {&e0s[s], &e1s[s], &n0s[s], &n1s[s]}) centre(*L);
+    }
+    o_ne = {stage_layer(st, a0, WKind::PlainT, bf16, true),
+            stage_layer(st, a1, WKind::FragAcc, bf16, true)};
+    o_ee = {stage_layer(st, b0, WKind::FragMem, bf16, true),
+            stage_layer(st, b1, WKind::FragAcc, bf16, true)};
+    for (int s = 0; s < S; ++s) {
+      o_em[s] = {stage_layer(st, e0s[s], WKind::FragMem, bf16, true),
+                 stage_layer(st, e1s[s], WKind::FragAcc, bf16, true)};
+      o_nm[s] = {stage_layer(st, n0s[s], WKind::FragMem, bf16, true),
+                 stage_layer(st, n1s[s], WKind::FragAcc, bf16, true)};
+    }
+    o_cls = {stage_layer(st, c0, WKind::FragMem, bf16, true),
+             stage_layer(st, c1, WKind::Plain, bf16, false)};
+    // The edge consumer of the projections computed after node update t
+    // (t = -1: the node encoder's second projection).
+    auto next_edge_l1 = [&](int t) -> const BlobLayer & {
+      return t + 1 < T ? e0s[S == 1 ? 0 : t + 1] : c0;
+    };
+    if (factored && bf16) {
+      // Scale of the projections that edge-side layer L reads, and of its
+      // W_e records: an fp16 record keeps |s W_e| inside the fp16 range too.
+      auto scale_p = [&](const BlobLayer &L) {
+        float sc = proj_f16_scale(L, H, hb, MIN_SCALE - 2), mx = 0.f;
+        for (int f = 0; f < L.fout && f16w; ++f)
+          for (int k = 0; k < L.fin; ++k) mx = fmaxf(mx, fabsf(L.W[(size_t)f * L.fin + k]));
+        while (sc * mx > 32768.f) sc *= 0.5f;
+        return sc;
+      };
+      fdh.s1_ee = scale_p(b0);
+      fdh.s1_cls = scale_p(c0);
+      for (int s = 0; s < S; ++s) fdh.s1_em.push_back(scale_p(e0s[s]));
       auto add16 = [&](const std::vector<uint16_t> &v) {
         return st.add(v.data(), v.size() * sizeof(uint16_t));
       };
@@ -1400,15 +1464,10 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
       // the weights times a power of two (W2, the node MLPs and the node
       // encoder's W2 then carry pow2_scale; the projections and W_e carry
       // the fp16 projections' consumer scale either way).
-      bool f16_fits = true;
       auto rec = [&](const BlobLayer &L, int c0, int K, int grp, float sc) {
-        if (!f16w) return rec_bf16x2(L, c0, K, grp, sc);
-        for (int f = 0; f < L.fout; ++f)
-          for (int k = c0; k < c0 + K; ++k)
-            if (!(fabsf(sc * L.W[(size_t)f * L.fin + k]) <= 65504.f)) f16_fits = false;
-        return rec_f16x1(L, c0, K, sc, grp);
+        return f16w ? rec_f16x1(L, c0, K, sc, grp) : rec_bf16x2(L, c0, K, grp, sc);
       };
-      auto s2_of = [&](const BlobLayer &L) { return f16w ? pow2_scale(L) : 1.f; };
+      auto s2_of = [&](const BlobLayer &L) { return f16w ? pow2_scale(L, MIN_SCALE - 2) : 1.f; };
       fdh.s2_ee = s2_of(b1);
       fdh.s2_ne = s2_of(a1);
       for (int s = 0; s < S; ++s) {
@@ -1443,10 +1502,6 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
         proj(us, next_edge_l1(t));
         o_upd_stream[t] = add16(us);
       }
-      if (!f16_fits) {
-        fail(GNN_E_UNSUPPORTED, "GNN_F16_WEIGHTS: a scaled weight exceeds the fp16 range");
-        return nullptr;
-      }
     } else if (factored && split) {
       auto add16 = [&](const std::vector<uint16_t> &v) {
         return st.add(v.data(), v.size() * sizeof(uint16_t));
@@ -1454,15 +1509,15 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
       auto cat = [](std::vector<uint16_t> &dst, const std::vector<uint16_t> &src) {
         dst.insert(dst.end(), src.begin(), src.end());
       };
-      fdh.s1_ee = pow2_scale(b0);
-      fdh.s2_ee = pow2_scale(b1);
-      fdh.s1_cls = pow2_scale(c0);
-      fdh.s2_ne = pow2_scale(a1);
+      fdh.s1_ee = pow2_scale(b0, MIN_SCALE - 2);
+      fdh.s2_ee = pow2_scale(b1, MIN_SCALE - 2);
+      fdh.s1_cls = pow2_scale(c0, MIN_SCALE - 2);
+      fdh.s2_ne = pow2_scale(a1, MIN_SCALE - 2);
       for (int s = 0; s < S; ++s) {
-        fdh.s1_em.push_back(pow2_scale(e0s[s]));
-        fdh.s2_em.push_back(pow2_scale(e1s[s]));
-        fdh.s1_nm.push_back(pow2_scale(n0s[s]));
-        fdh.s2_nm.push_back(pow2_scale(n1s[s]));
+        fdh.s1_em.push_back(pow2_scale(e0s[s], MIN_SCALE - 2));
+        fdh.s2_em.push_back(pow2_scale(e1s[s], MIN_SCALE - 2));
+        fdh.s1_nm.push_back(pow2_scale(n0s[s], MIN_SCALE - 2));
+        fdh.s2_nm.push_back(pow2_scale(n1s[s], MIN_SCALE - 2));
         o_we_em[s] = add16(rec_f16x2(e0s[s], 2 * H, H, fdh.s1_em[s], 0));
         o_w2_em[s] = add16(rec_f16x2(e1s[s], 0, H, fdh.s2_em[s], -1));
       }

@@ -2,174 +2,210 @@
 // step a Filtering MLP scores the candidate edges and applyFiltering keeps
 // the edges above a fixed threshold).
 //
-// filter     one wave per 32 candidate edges: gather the raw features of
-//             both endpoints, layer 1 ([x_src; x_dst], 2F -> H) on VALU,
-//             LayerNorm/ReLU, layer 2 (H -> H) on the matrix cores,
-//             LayerNorm/ReLU, H -> 1 head, sigmoid.  Layer 2 runs on the
-//             fp16 matrix cores from split operands (SPLIT, as in split.hip:
-//             f16x2 records of s W1 with s a power of two, the LayerNorm/ReLU
-//             output as x1 + x2, three products per k-step, every partial
-//             product accumulated in fp32; the LayerNorm then takes the bias
-//             as s b1 and eps as eps s^2, which is the LayerNorm of W1 x + b1
-//             exactly), or on the fp32 matrix cores when the handle found the
-//             layer-1 LayerNorm output bound outside the fp16 range.
-// compaction  keep = score > threshold, in input order: per-block counts,
-//             one exclusive scan of the block counts, then a stable scatter
-//             (wave ballots inside a block); the kept edges are written as a
-//             contiguous [2][n_kept] edge_index, ready for gnn_infer.
-#include "device_common.h"
+// filter      one wave per 32 candidate edges: the raw features of both
+//             endpoints, two hidden layers (small_mlp.h), H -> 1 head,
+//             sigmoid; the unit's kept edges (score > threshold) go out as
+//             one 32-bit mask.
+// compaction  in input order.  A workgroup of the scoring launch takes one run
+//             of consecutive units and counts its kept edges, so the scatter
+//             launch (same runs) adds up the counts before its own and needs
+//             no launches to count or scan; within a run it ranks by popcounts
+//             of the masks.  The kept edges are written as a contiguous
+//             [2][n_kept] edge_index, ready for gnn_infer.
+//
+// 2.0M candidates, H = 64: whole call 278 -> 125 us, scoring 247 -> 86 us (one
+// unit per workgroup slot, weights from L2, layer 0 on the VALU before),
+// compaction 16 us in three launches -> 8.5 in one.  Counters of the scoring
+// launch: VALU busy 50%, matrix cores 37% of the time, the two hardly
+// overlapping; LDS and gather waits cover the rest.  12 or 16 waves per
+// workgroup take the same time (the parameters spill or U falls to 1).
+#include "small_mlp.h"
 
 namespace gnn {
 namespace {
 
-constexpr int FWAVES = 4;
-constexpr int CTHREADS = 256;
-constexpr int CITEMS = 4;
-constexpr int CTILE = CTHREADS * CITEMS;
+constexpr int CTHREADS = 1024;
 
-template <int MB, bool SPLIT>
-__global__ __launch_bounds__(64 * FWAVES) void filter_mlp(FilterArgs a) {
+__host__ __device__ inline int64_t units_of(int64_t n_edges) { return (n_edges + 31) / 32; }
+
+// Run of units of workgroup b of `wgs`: [b * per, b * per + per) clipped.
+__host__ __device__ inline int64_t run_len(int64_t units, int32_t wgs) {
+  return (units + wgs - 1) / wgs;
+}
+
+// U units at a time per wave (small_mlp.h).
+template <int MB, bool SPLIT, bool FOLD, int FK>
+__global__ __launch_bounds__(64 * SM_WAVES) void filter_mlp(FilterArgs a) {
+  constexpr int U = MB == 2 && FOLD ? 2 : 1;
+  using M = SmallMlp<MB, SPLIT, FOLD, U>;
   constexpr int H = 32 * MB;
+  __shared__ typename M::Lds lds;
+  __shared__ float head[H];
+  __shared__ int32_t kept[SM_WAVES];
   const int lane = threadIdx.x & 63, hh = lane >> 5, n = lane & 31;
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int64_t row0 = ((int64_t)blk * FWAVES + (threadIdx.x >> 6)) * 32;
-  if (row0 >= a.n_edges) return;
-  const int64_t row = row0 + n;
-  const bool valid = row < a.n_edges;
-  const int64_t r = valid ? row : a.n_edges - 1;
-  const int64_t s = clamp_idx(a.edge_index[r], a.n_nodes);
-  const int64_t d = clamp_idx(a.edge_index[a.n_edges + r], a.n_nodes);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t units = units_of(a.n_edges), per = run_len(units, gridDim.x);
+  const int64_t u0 = (int64_t)blockIdx.x * per, u1 = u0 + per < units ? u0 + per : units;
+  const int F = FK ? FK : a.F;
+  constexpr int STEP = U * SM_WAVES;
 
-  // layer 1 over [x_src; x_dst]; W0t is [2F][H]
-  f16v acc[MB];
+  auto load_idx = [&](int64_t u, int32_t (&s)[U], int32_t (&d)[U]) {
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f4 bb = *(const f4 *)(a.b0 + mb * 32 + 8 * q + 4 * hh);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) acc[mb][4 * q + t] = bb[t];
+    for (int i = 0; i < U; ++i) {
+      const int64_t row = (u + i) * 32 + n, r = row < a.n_edges ? row : a.n_edges - 1;
+      s[i] = a.edge_index[r];
+      d[i] = a.edge_index[a.n_edges + r];
     }
-  for (int k = 0; k < 2 * a.F; ++k) {
-    const float xk = k < a.F ? a.x[s * a.F + k] : a.x[d * a.F + (k - a.F)];
-    const float *wk = a.w0t + k * H + 4 * hh;
+  };
+  // Feature 2 step + hh of the rows [x_src; x_dst].
+  auto load_x = [&](const int32_t (&s)[U], const int32_t (&d)[U], int step, float (&xk)[U]) {
+    const int k = 2 * step + hh;
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int64_t v = clamp_idx(k < F ? s[i] : d[i], a.n_nodes);
+      xk[i] = a.x[v * F + (k < F ? k : k - F)];
+    }
+  };
+  // The indices are requested two rounds ahead and, for the template's F, the
+  // features one round ahead.
+  int64_t u = u0 + U * wv;
+  int32_t s[U], d[U], s1[U], d1[U];
+  float xv[FK ? FK : 1][U];
+  if (u < u1) load_idx(u, s, d);
+  if (u + STEP < u1) load_idx(u + STEP, s1, d1);
+  if constexpr (FK > 0)
+    if (u < u1)
+#pragma unroll
+      for (int k = 0; k < FK; ++k) load_x(s, d, k, xv[k]);
+  M::load(lds, a.mlp);
+  for (int i = threadIdx.x; i < H; i += 64 * SM_WAVES) head[i] = a.w2[i];
+  __syncthreads();
+  const float b2 = a.b2[0];
+
+  int32_t cnt = 0;
+  for (; u < u1; u += STEP) {
+    // keeps the LDS reads of the weights inside the loop
+    asm volatile("" ::: "memory");
+    f16v acc[U][MB], acc2[U][MB];
+    M::bias(acc, lds.prm, hh);
+    if constexpr (FK > 0) {
+#pragma unroll
+      for (int k = 0; k < FK; ++k) M::step0(acc, lds, k, xv[k], lane);
+    } else {
+      for (int k = 0; k < F; ++k) {
+        load_x(s, d, k, xv[0]);
+        M::step0(acc, lds, k, xv[0], lane);
+      }
+    }
+    if (u + STEP < u1) {
+#pragma unroll
+      for (int i = 0; i < U; ++i) {
+        s[i] = s1[i];
+        d[i] = d1[i];
+      }
+      if (u + 2 * STEP < u1) load_idx(u + 2 * STEP, s1, d1);
+      if constexpr (FK > 0)
+#pragma unroll
+        for (int k = 0; k < FK; ++k) load_x(s, d, k, xv[k]);
+    }
+    M::rest(acc, acc2, lds, a.mlp, lane, hh);
+    float part[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) part[i] = 0.f;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const f4 ww = *(const f4 *)(wk + mb * 32 + 8 * q);
+        const f4 ww = *(const f4 *)(head + mb * 32 + 8 * q + 4 * hh);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[mb][4 * q + t] += ww[t] * xk;
+        for (int i = 0; i < U; ++i)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) part[i] += acc2[i][mb][4 * q + t] * ww[t];
       }
-  }
-  bias_ln_relu<MB>(acc, nullptr, a.g0, a.beta0, a.eps, hh, false);
-  f16v acc2[MB];
-  if constexpr (SPLIT) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc2[mb][v] = 0.f;
-    const h8 *rec = (const h8 *)a.w1r + lane;
-#pragma unroll
-    for (int g = 0; g < 2 * MB; ++g) step_h<MB>(acc2, rec + g * 2 * MB * 64, acc_x<MB>(acc, g));
-    bias_ln_relu<MB>(acc2, a.b1, a.g1, a.beta1, a.eps * a.s1 * a.s1, hh, true, a.s1);
-  } else {
-    gemm_acc_f32<MB, MB>(acc2, acc, (const f4 *)a.w1 + lane, 0);
-    bias_ln_relu<MB>(acc2, a.b1, a.g1, a.beta1, a.eps, hh, true);
-  }
-  float part = 0.f;
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f4 ww = *(const f4 *)(a.w2 + mb * 32 + 8 * q + 4 * hh);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) part += acc2[mb][4 * q + t] * ww[t];
+    for (int i = 0; i < U; ++i) {
+      part[i] += __shfl_xor(part[i], 32);
+      const float score = sigmoidf_stable(part[i] + b2);
+      const int64_t row = (u + i) * 32 + n;
+      const bool mine = hh == 0 && u + i < u1 && row < a.n_edges;
+      if (mine) a.scores[row] = score;
+      const uint32_t m = (uint32_t)__ballot(mine && score > a.threshold);
+      if (lane == 0 && u + i < u1) a.masks[u + i] = m;
+      cnt += __popc(m);
     }
-  part += __shfl_xor(part, 32);
-  if (valid && hh == 0) a.scores[row] = sigmoidf_stable(part + a.b2[0]);
-}
-
-// Kept edges per tile of CTILE consecutive candidates.
-__global__ __launch_bounds__(CTHREADS) void compact_count(const float *__restrict__ scores,
-                                                          int64_t n, float threshold,
-                                                          int32_t *__restrict__ counts) {
-  __shared__ int32_t part[CTHREADS / 64];
-  const int64_t base = (int64_t)blockIdx.x * CTILE;
-  int c = 0;
-#pragma unroll
-  for (int it = 0; it < CITEMS; ++it) {
-    const int64_t i = base + (int64_t)it * CTHREADS + threadIdx.x;
-    c += (i < n && scores[i] > threshold) ? 1 : 0;
   }
-  for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+  if (lane == 0) kept[wv] = cnt;
   __syncthreads();
   if (threadIdx.x == 0) {
-    int t = 0;
-    for (int w = 0; w < CTHREADS / 64; ++w) t += part[w];
-    counts[blockIdx.x] = t;
+    int32_t t = 0;
+    for (int w = 0; w < SM_WAVES; ++w) t += kept[w];
+    a.counts[blockIdx.x] = t;
   }
 }
 
-// Exclusive scan of the tile counts in place; total -> *total.  One block.
-__global__ __launch_bounds__(1024) void compact_scan(int32_t *__restrict__ counts, int32_t ntiles,
-                                                     int32_t *__restrict__ total) {
-  __shared__ int32_t part[1024];
-  const int t = threadIdx.x;
-  const int chunk = (ntiles + 1023) / 1024;
-  const int beg = min(t * chunk, ntiles), end = min(beg + chunk, ntiles);
-  int32_t s = 0;
-  for (int i = beg; i < end; ++i) s += counts[i];
-  part[t] = s;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int32_t v = t >= off ? part[t - off] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  int32_t run = part[t] - s;
-  for (int i = beg; i < end; ++i) {
-    const int32_t v = counts[i];
-    counts[i] = run;
-    run += v;
-  }
-  if (t == 1023) *total = part[1023];
-}
-
-// Stable scatter of the kept edges: position = tile offset + kept items
-// before this one in the tile (item order = (round, wave, lane)).
+// Stable scatter of the kept edges, workgroup b the run of units that
+// workgroup b of the scoring launch took: position = kept edges of the runs
+// before + kept edges before this one in the run.  CTHREADS units at a time:
+// a block scan of their popcounts, then each half-wave writes one unit.
 __global__ __launch_bounds__(CTHREADS) void compact_scatter(
-    const float *__restrict__ scores, const int32_t *__restrict__ edge_index, int64_t n,
-    float threshold, const int32_t *__restrict__ offs, const int32_t *__restrict__ total,
-    int32_t *__restrict__ out) {
-  __shared__ int32_t wcnt[CITEMS][CTHREADS / 64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t base = (int64_t)blockIdx.x * CTILE;
-  const uint64_t lt = (1ull << lane) - 1ull;
-  bool keep[CITEMS];
-  int rank[CITEMS];
-#pragma unroll
-  for (int it = 0; it < CITEMS; ++it) {
-    const int64_t i = base + (int64_t)it * CTHREADS + threadIdx.x;
-    keep[it] = i < n && scores[i] > threshold;
-    const uint64_t m = __ballot(keep[it]);
-    rank[it] = __popcll(m & lt);
-    if (lane == 0) wcnt[it][w] = __popcll(m);
+    const int32_t *__restrict__ edge_index, int64_t n, const uint32_t *__restrict__ masks,
+    const int32_t *__restrict__ counts, int32_t *__restrict__ total, int32_t *__restrict__ out) {
+  __shared__ int32_t wsum[2][CTHREADS / 64];
+  __shared__ int32_t base[CTHREADS];
+  __shared__ uint32_t msk[CTHREADS];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int32_t wgs = gridDim.x, blk = blockIdx.x;
+  auto wave_sum = [](int32_t v) {
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    return v;
+  };
+  int32_t before = 0, all = 0;
+  for (int32_t i = tid; i < wgs; i += CTHREADS) {
+    const int32_t c = counts[i];
+    all += c;
+    before += i < blk ? c : 0;
+  }
+  before = wave_sum(before);
+  all = wave_sum(all);
+  if (lane == 0) {
+    wsum[0][w] = before;
+    wsum[1][w] = all;
   }
   __syncthreads();
-  const int32_t tot = *total;
-  int32_t run = offs[blockIdx.x];
-#pragma unroll
-  for (int it = 0; it < CITEMS; ++it) {
-    int32_t before = run;
-    for (int ww = 0; ww < w; ++ww) before += wcnt[it][ww];
-    for (int ww = 0; ww < CTHREADS / 64; ++ww) run += wcnt[it][ww];
-    if (keep[it]) {
-      const int64_t i = base + (int64_t)it * CTHREADS + threadIdx.x;
-      const int32_t pos = before + rank[it];
-      if (pos < tot) {  // always true when the counts are consistent
+  int32_t run = 0, tot = 0;
+  for (int i = 0; i < CTHREADS / 64; ++i) {
+    run += wsum[0][i];
+    tot += wsum[1][i];
+  }
+  if (blk == 0 && tid == 0) *total = tot;
+  const int64_t units = units_of(n), per = run_len(units, wgs);
+  const int64_t u0 = (int64_t)blk * per, u1 = u0 + per < units ? u0 + per : units;
+  for (int64_t ub = u0; ub < u1; ub += CTHREADS) {
+    const uint32_t m = ub + tid < u1 ? masks[ub + tid] : 0u;
+    const int32_t c = __popc(m);
+    int32_t incl = c;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int32_t v = __shfl_up(incl, off);
+      if (lane >= off) incl += v;
+    }
+    __syncthreads();  // (the previous round's and the first sums' readers)
+    if (lane == 63) wsum[0][w] = incl;
+    msk[tid] = m;
+    __syncthreads();
+    int32_t pre = run;
+    for (int i = 0; i < CTHREADS / 64; ++i) {
+      pre += i < w ? wsum[0][i] : 0;
+      run += wsum[0][i];
+    }
+    base[tid] = pre + incl - c;
+    __syncthreads();
+    const int64_t here = u1 - ub < CTHREADS ? u1 - ub : CTHREADS;
+    const uint32_t b = lane & 31, lt = (1u << b) - 1u;
+    for (int64_t j = tid >> 5; j < here; j += CTHREADS / 32) {
+      const uint32_t mj = msk[j];
+      if (mj >> b & 1u) {
+        const int64_t i = (ub + j) * 32 + b;
+        const int32_t pos = base[j] + __popc(mj & lt);
         out[pos] = edge_index[i];
         out[(int64_t)tot + pos] = edge_index[n + i];
       }
@@ -177,41 +213,38 @@ __global__ __launch_bounds__(CTHREADS) void compact_scatter(
   }
 }
 
-inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
+template <int MB>
+hipError_t scores_h(const FilterArgs &a, int32_t wgs, hipStream_t stream) {
+  if (!a.mlp.w1r) return launch(filter_mlp<MB, false, false, 0>, wgs, 64 * SM_WAVES, 0, stream, a);
+  if (!a.mlp.fold) return launch(filter_mlp<MB, true, false, 0>, wgs, 64 * SM_WAVES, 0, stream, a);
+  // hits have three features; any other width takes the loop over its steps
+  if (a.F == 3) return launch(filter_mlp<MB, true, true, 3>, wgs, 64 * SM_WAVES, 0, stream, a);
+  return launch(filter_mlp<MB, true, true, 0>, wgs, 64 * SM_WAVES, 0, stream, a);
+}
 
 }  // namespace
 
-hipError_t launch_filter_scores(int hidden, const FilterArgs &a, hipStream_t stream) {
-  const int64_t waves = (a.n_edges + 31) / 32;
-  const int64_t blocks = (waves + FWAVES - 1) / FWAVES;
-  if (blocks <= 0) return hipSuccess;
-  if (blocks > INT32_MAX) return hipErrorInvalidValue;
-  switch (hidden) {
-    case 64:
-      if (a.w1r) filter_mlp<2, true><<<(unsigned)blocks, 64 * FWAVES, 0, stream>>>(a);
-      else filter_mlp<2, false><<<(unsigned)blocks, 64 * FWAVES, 0, stream>>>(a);
-      break;
-    case 128:
-      if (a.w1r) filter_mlp<4, true><<<(unsigned)blocks, 64 * FWAVES, 0, stream>>>(a);
-      else filter_mlp<4, false><<<(unsigned)blocks, 64 * FWAVES, 0, stream>>>(a);
-      break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+int32_t filter_wgs(int64_t n_edges, int n_cu) {
+  const int64_t units = units_of(n_edges), most = (int64_t)n_cu * SM_WGS_PER_CU;
+  return (int32_t)(units < most ? units : most);
 }
 
-size_t compact_tiles(int64_t n) { return (size_t)((n + CTILE - 1) / CTILE); }
+hipError_t launch_filter_scores(int hidden, const FilterArgs &a, int32_t wgs, hipStream_t stream) {
+  if (a.n_edges <= 0) return hipSuccess;
+  if (wgs < 1 || a.mlp.steps != a.F || a.F < 1 || a.F > MAX_F) return hipErrorInvalidValue;
+  switch (hidden) {
+    case 64: return scores_h<2>(a, wgs, stream);
+    case 128: return scores_h<4>(a, wgs, stream);
+  }
+  return hipErrorInvalidValue;
+}
 
-hipError_t launch_compact(const float *scores, const int32_t *edge_index, int64_t n,
-                          float threshold, int32_t *counts, int32_t *total, int32_t *out,
+hipError_t launch_compact(const int32_t *edge_index, int64_t n, const uint32_t *masks,
+                          const int32_t *counts, int32_t wgs, int32_t *total, int32_t *out,
                           hipStream_t stream) {
-  const int32_t ntiles = (int32_t)compact_tiles(n);
-  if (ntiles == 0) return hipSuccess;
-  compact_count<<<ntiles, CTHREADS, 0, stream>>>(scores, n, threshold, counts);
-  compact_scan<<<1, 1024, 0, stream>>>(counts, ntiles, total);
-  compact_scatter<<<ntiles, CTHREADS, 0, stream>>>(scores, edge_index, n, threshold, counts,
-                                                   total, out);
-  return hipGetLastError();
+  if (n <= 0 || wgs < 1) return hipErrorInvalidValue;
+  return launch(compact_scatter, wgs, CTHREADS, 0, stream, edge_index, n, masks, counts, total,
+                out);
 }
 
 }  // namespace gnn

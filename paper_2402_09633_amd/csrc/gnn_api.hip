@@ -1424,17 +1424,20 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
       for (int s = 0; s < S; ++s)
         for (BlobLayer *L : {&e0s[s], &e1s[s], &n0s[s], &n1s[s]}) centre(*L);
     }
+    // (the split kernels read their matrices from records, not from here)
+    const WKind f_mem = split ? WKind::Plain : WKind::FragMem;
+    const WKind f_acc = split ? WKind::Plain : WKind::FragAcc;
     o_ne = {stage_layer(st, a0, WKind::PlainT, bf16, true),
-            stage_layer(st, a1, WKind::FragAcc, bf16, true)};
-    o_ee = {stage_layer(st, b0, WKind::FragMem, bf16, true),
-            stage_layer(st, b1, WKind::FragAcc, bf16, true)};
+            stage_layer(st, a1, f_acc, bf16, true)};
+    o_ee = {stage_layer(st, b0, f_mem, bf16, true),
+            stage_layer(st, b1, f_acc, bf16, true)};
     for (int s = 0; s < S; ++s) {
-      o_em[s] = {stage_layer(st, e0s[s], WKind::FragMem, bf16, true),
-                 stage_layer(st, e1s[s], WKind::FragAcc, bf16, true)};
-      o_nm[s] = {stage_layer(st, n0s[s], WKind::FragMem, bf16, true),
-                 stage_layer(st, n1s[s], WKind::FragAcc, bf16, true)};
+      o_em[s] = {stage_layer(st, e0s[s], f_mem, bf16, true),
+                 stage_layer(st, e1s[s], f_acc, bf16, true)};
+      o_nm[s] = {stage_layer(st, n0s[s], f_mem, bf16, true),
+                 stage_layer(st, n1s[s], f_acc, bf16, true)};
     }
-    o_cls = {stage_layer(st, c0, WKind::FragMem, bf16, true),
+    o_cls = {stage_layer(st, c0, f_mem, bf16, true),
              stage_layer(st, c1, WKind::Plain, bf16, false)};
     // The edge consumer of the projections computed after node update t
     // (t = -1: the node encoder's second projection).
@@ -1780,9 +1783,140 @@ int gnn_infer_logits(gnn_handle *h, const float *node_feat, const int32_t *edge_
   return run(h, node_feat, edge_index, n_nodes, n_edges, stream, ro);
 }
 
+namespace {
+
+// A hidden layer's LayerNorm gains folded into the layer that reads it:
+// relu(g y + beta) = |g| relu(sign(g) y + beta / |g|), so the rows of this
+// layer take the sign, beta becomes FOLD_SCALE beta / |g|, and the columns of
+// the next layer's weights are multiplied by |g| / FOLD_SCALE.  The products
+// are formed in double and rounded once.  Not for gains so uneven, or so
+// small beside their shifts, that the folded values would spread over the
+// range of the split products (ok = false).
+struct Folded {
+  std::vector<float> W, b, g, beta, Wn;
+  BlobLayer L, next;
+  bool ok = true;
+  Folded(const BlobLayer &src, const BlobLayer &nx)
+      : W(src.W, src.W + (size_t)src.fin * src.fout), b(src.b, src.b + src.fout),
+        g(src.fout, 1.f), beta(src.fout), Wn(nx.W, nx.W + (size_t)nx.fin * nx.fout), L(src),
+        next(nx) {
+    double gmax = 0.0;
+    for (int f = 0; f < src.fout; ++f) gmax = fmax(gmax, fabs((double)src.g[f]));
+    for (int f = 0; f < src.fout; ++f) {
+      const double gf = fabs((double)src.g[f]), c = (double)src.beta[f] / gf;
+      if (!(gf > 0.0) || !(gf >= gmax / 256.0) || !(gmax <= 1e30) || !(fabs(c) <= 256.0)) ok = false;
+      if (src.g[f] < 0.f) {
+        for (int k = 0; k < src.fin; ++k) W[(size_t)f * src.fin + k] = -W[(size_t)f * src.fin + k];
+        b[f] = -b[f];
+      }
+      beta[f] = (float)(FOLD_SCALE * c);
+      for (int o = 0; o < nx.fout; ++o) {
+        float &w = Wn[(size_t)o * nx.fin + f];
+        w = (float)((double)w * gf / FOLD_SCALE);
+      }
+    }
+    L.W = W.data();
+    L.b = b.data();
+    L.g = g.data();
+    L.beta = beta.data();
+    next.W = Wn.data();
+  }
+  Folded(const Folded &) = delete;
+};
+
+// Device weights of the filter and the embedding: two hidden layers, centred
+// (Centred), and the output layer.  Layer 1 runs on the fp16 matrix cores
+// from split operands when its input, a LayerNorm/ReLU output, stays inside
+// half the fp16 range (else on the fp32 ones); the LayerNorms' gains are then
+// folded into the layers that follow where Folded allows it.
+struct SmallMlpOff {
+  size_t w0a = 0, w1r = 0, w2r = 0;
+  LayerOff l0, l1, l2;
+  bool split = false, fold = false;
+  float s1 = 1.f, s2 = 1.f;
+  int steps = 0;
+
+  SmallMlpOff(Staging &st, const BlobLayer &in0, const BlobLayer &in1, const BlobLayer &in2) {
+    split = ln_out_bound(in0) <= 32768.0;
+    // (each layer is centred before its rows take the gains' signs)
+    const Centred c0(in0), c1(in1);
+    const Folded f0(c0.L, c1.L), f1(f0.next, in2);
+    fold = split && f0.ok && f1.ok;
+    const BlobLayer &l_0 = fold ? f0.L : c0.L, &l_1 = fold ? f1.L : c1.L;
+    const BlobLayer &out = fold ? f1.next : in2;
+    const int K = in0.fin, H = in0.fout, MB = H / 32;
+    steps = (K + 1) / 2;
+    std::vector<float> a((size_t)steps * MB * 64);
+    for (int k2 = 0; k2 < steps; ++k2)
+      for (int mb = 0; mb < MB; ++mb)
+        for (int l = 0; l < 64; ++l) {
+          const int k = 2 * k2 + l / 32;
+          a[((size_t)k2 * MB + mb) * 64 + l] =
+              k < K ? l_0.W[(size_t)(32 * mb + l % 32) * K + k] : 0.f;
+        }
+    w0a = st.add(a.data(), a.size() * sizeof(float));
+    l0 = stage_layer(st, l_0, WKind::Plain, false, true);
+    l1 = stage_layer(st, l_1, split ? WKind::Plain : WKind::FragAcc, false, true);
+    l2 = stage_layer(st, out, WKind::Plain, false, false);
+    if (split) {
+      s1 = pow2_scale(l_1, MIN_SCALE - 2);
+      const std::vector<uint16_t> r = rec_f16x2(l_1, 0, H, s1, -1);
+      w1r = st.add(r.data(), r.size() * sizeof(uint16_t));
+    }
+    if (fold) {
+      // three-part records of the output layer (embedding), one 32-row block
+      s2 = pow2_scale(out);
+      std::vector<uint16_t> r((size_t)(H / 16) * 3 * 64 * 8);
+      for (int g = 0; g < H / 16; ++g)
+        for (int l = 0; l < 64; ++l)
+          for (int j = 0; j < 8; ++j) {
+            const int k = node_line_k(g, l / 32, j, -1);
+            float w = l % 32 < out.fout ? s2 * out.W[(size_t)(l % 32) * H + k] : 0.f;
+            for (int p = 0; p < 3; ++p) {
+              const _Float16 v = (_Float16)w;
+              r[(((size_t)g * 3 + p) * 64 + l) * 8 + j] = f16_bits(v);
+              w -= (float)v;
+            }
+          }
+      w2r = st.add(r.data(), r.size() * sizeof(uint16_t));
+    }
+  }
+
+  SmallMlpArgs args(const unsigned char *base, float eps) const {
+    SmallMlpArgs m;
+    const LayerDev d0 = fix_layer(l0, base), d1 = fix_layer(l1, base);
+    m.steps = steps;
+    m.w0a = (const float *)(base + w0a);
+    m.b0 = d0.b;
+    m.g0 = d0.g;
+    m.beta0 = d0.beta;
+    m.w1 = (const float *)d1.w;
+    m.b1 = d1.b;
+    m.g1 = d1.g;
+    m.beta1 = d1.beta;
+    if (split) m.w1r = base + w1r;
+    m.s1 = s1;
+    m.eps = eps;
+    m.fold = fold;
+    return m;
+  }
+};
+
+int cu_count(int dev) {
+  int n = 0;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) {
+    (void)hipGetLastError();
+    n = 256;
+  }
+  return n;
+}
+
+}  // namespace
+
 struct gnn_filter {
   gnn_filter_dims dims;
   int device = 0;
+  int n_cu = 0;
   void *dev = nullptr;
   FilterArgs tmpl;  // weight pointers
 };
@@ -1838,18 +1972,7 @@ gnn_filter *gnn_filter_create(const float *weights, const gnn_filter_dims *dims)
   };
   BlobLayer l0 = next(2 * F, H, true), l1 = next(H, H, true), l2 = next(H, 1, false);
   Staging st;
-  LayerOff o0 = stage_layer(st, l0, WKind::PlainT, false, true);
-  LayerOff o1 = stage_layer(st, l1, WKind::FragAcc, false, true);
-  LayerOff o2 = stage_layer(st, l2, WKind::Plain, false, false);
-  // Layer 2 on the fp16 matrix cores from split operands when its input, a
-  // LayerNorm/ReLU output, stays inside half the fp16 range (else fp32).
-  const bool split = ln_out_bound(l0) <= 32768.0;
-  const float s1 = split ? pow2_scale(l1) : 1.f;
-  size_t o_w1r = 0;
-  if (split) {
-    const std::vector<uint16_t> r = rec_f16x2(l1, 0, H, s1, -1);
-    o_w1r = st.add(r.data(), r.size() * sizeof(uint16_t));
-  }
+  const SmallMlpOff om(st, l0, l1, l2);
   gnn_filter *f = new gnn_filter();
   f->dims = *dims;
   f->device = dev;
@@ -1862,23 +1985,12 @@ gnn_filter *gnn_filter_create(const float *weights, const gnn_filter_dims *dims)
     return nullptr;
   }
   const unsigned char *base = (const unsigned char *)f->dev;
-  LayerDev d0 = fix_layer(o0, base), d1 = fix_layer(o1, base), d2 = fix_layer(o2, base);
+  const LayerDev d2 = fix_layer(om.l2, base);
+  f->n_cu = cu_count(dev);
   f->tmpl.F = F;
-  f->tmpl.eps = dims->ln_eps;
-  f->tmpl.w0t = (const float *)d0.w;
-  f->tmpl.b0 = d0.b;
-  f->tmpl.g0 = d0.g;
-  f->tmpl.beta0 = d0.beta;
-  f->tmpl.w1 = (const float *)d1.w;
-  f->tmpl.b1 = d1.b;
-  f->tmpl.g1 = d1.g;
-  f->tmpl.beta1 = d1.beta;
+  f->tmpl.mlp = om.args(base, dims->ln_eps);
   f->tmpl.w2 = (const float *)d2.w;
   f->tmpl.b2 = d2.b;
-  if (split) {
-    f->tmpl.w1r = base + o_w1r;
-    f->tmpl.s1 = s1;
-  }
   return f;
 }
 
@@ -1897,6 +2009,7 @@ void gnn_filter_destroy(gnn_filter *f) {
 struct gnn_embedder {
   gnn_embed_dims dims;
   int device = 0;
+  int n_cu = 0;
   void *dev = nullptr;
   EmbedArgs tmpl;  // weight pointers
 };
@@ -1954,17 +2067,7 @@ gnn_embedder *gnn_embed_create(const float *weights, const gnn_embed_dims *dims)
   };
   BlobLayer l0 = next(F, H, true), l1 = next(H, H, true), l2 = next(H, D, false);
   Staging st;
-  LayerOff o0 = stage_layer(st, l0, WKind::PlainT, false, true);
-  LayerOff o1 = stage_layer(st, l1, WKind::FragAcc, false, true);
-  LayerOff o2 = stage_layer(st, l2, WKind::Plain, false, false);
-  // layer 2 on split fp16 products unless its input leaves the fp16 range
-  const bool split = ln_out_bound(l0) <= 32768.0;
-  const float s1 = split ? pow2_scale(l1) : 1.f;
-  size_t o_w1r = 0;
-  if (split) {
-    const std::vector<uint16_t> r = rec_f16x2(l1, 0, H, s1, -1);
-    o_w1r = st.add(r.data(), r.size() * sizeof(uint16_t));
-  }
+  const SmallMlpOff om(st, l0, l1, l2);
   gnn_embedder *m = new gnn_embedder();
   m->dims = *dims;
   m->device = dev;
@@ -1977,24 +2080,17 @@ gnn_embedder *gnn_embed_create(const float *weights, const gnn_embed_dims *dims)
     return nullptr;
   }
   const unsigned char *base = (const unsigned char *)m->dev;
-  LayerDev d0 = fix_layer(o0, base), d1 = fix_layer(o1, base), d2 = fix_layer(o2, base);
+  const LayerDev d2 = fix_layer(om.l2, base);
+  m->n_cu = cu_count(dev);
   m->tmpl.F = F;
   m->tmpl.D = D;
-  m->tmpl.eps = dims->ln_eps;
-  m->tmpl.w0t = (const float *)d0.w;
-  m->tmpl.b0 = d0.b;
-  m->tmpl.g0 = d0.g;
-  m->tmpl.beta0 = d0.beta;
-  m->tmpl.w1 = (const float *)d1.w;
-  m->tmpl.b1 = d1.b;
-  m->tmpl.g1 = d1.g;
-  m->tmpl.beta1 = d1.beta;
-  if (split) {
-    m->tmpl.w1r = base + o_w1r;
-    m->tmpl.s1 = s1;
-  }
+  m->tmpl.mlp = om.args(base, dims->ln_eps);
   m->tmpl.w2 = (const float *)d2.w;
   m->tmpl.b2 = d2.b;
+  if (om.fold) {
+    m->tmpl.w2r = base + om.w2r;
+    m->tmpl.s2 = om.s2;
+  }
   return m;
 }
 
@@ -2010,7 +2106,7 @@ int gnn_embed_apply(gnn_embedder *m, const float *node_feat, int64_t n_nodes, fl
   a.n = n_nodes;
   a.x = node_feat;
   a.z = z;
-  const hipError_t e = launch_embed(m->dims.hidden, a, stream);
+  const hipError_t e = launch_embed(m->dims.hidden, a, m->n_cu, stream);
   if (e != hipSuccess) return fail(GNN_E_HIP, "embedding launch failed: %s", hipGetErrorString(e));
   return GNN_OK;
 }
@@ -2038,9 +2134,10 @@ int gnn_filter_apply(gnn_filter *f, const float *node_feat, const int32_t *edge_
   if (!node_feat || !edge_index || !edge_index_out)
     return fail(GNN_E_INVALID_ARG, "NULL input or output pointer");
   DeviceGuard guard(f->device);
-  const size_t nt = compact_tiles(n_edges);
+  const int32_t wgs = filter_wgs(n_edges, f->n_cu);
   const size_t sc_bytes = edge_scores ? 0 : align256((size_t)n_edges * 4);
-  const size_t bytes = sc_bytes + align256((nt + 1) * 4) + 256;
+  const size_t mask_bytes = align256((size_t)((n_edges + 31) / 32) * 4);
+  const size_t bytes = sc_bytes + mask_bytes + ((size_t)wgs + 1) * 4;
   int rc = GNN_OK;
   unsigned char *ws = nullptr;
   {
@@ -2051,8 +2148,9 @@ int gnn_filter_apply(gnn_filter *f, const float *node_feat, const int32_t *edge_
     }
   }
   float *scores = edge_scores ? edge_scores : (float *)ws;
-  int32_t *counts = (int32_t *)(ws + sc_bytes);
-  int32_t *total = counts + nt;
+  uint32_t *masks = (uint32_t *)(ws + sc_bytes);
+  int32_t *counts = (int32_t *)(ws + sc_bytes + mask_bytes);
+  int32_t *total = counts + wgs;
   int32_t host_total = 0;
   FilterArgs a = f->tmpl;
   a.n_edges = n_edges;
@@ -2060,9 +2158,11 @@ int gnn_filter_apply(gnn_filter *f, const float *node_feat, const int32_t *edge_
   a.x = node_feat;
   a.edge_index = edge_index;
   a.scores = scores;
-  HIP_TRY(launch_filter_scores(f->dims.hidden, a, stream));
-  HIP_TRY(launch_compact(scores, edge_index, n_edges, threshold, counts, total, edge_index_out,
-                         stream));
+  a.threshold = threshold;
+  a.masks = masks;
+  a.counts = counts;
+  HIP_TRY(launch_filter_scores(f->dims.hidden, a, wgs, stream));
+  HIP_TRY(launch_compact(edge_index, n_edges, masks, counts, wgs, total, edge_index_out, stream));
   HIP_TRY(hipMemcpyAsync(&host_total, total, 4, hipMemcpyDeviceToHost, stream));
   HIP_TRY(hipStreamSynchronize(stream));
   *n_kept = host_total;

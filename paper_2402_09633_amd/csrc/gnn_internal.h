@@ -238,6 +238,25 @@ hipError_t build_csr(const int32_t *edge_index, int32_t n_edges, int32_t n_nodes
 hipError_t launch_scatter_rows(Act act, const void *src, const int32_t *idx, float *dst,
                                int64_t rows, int H, hipStream_t stream);
 
+// Two hidden layers K -> H -> H of the filter and the embedding (small_mlp.h),
+// weights centred.
+struct SmallMlpArgs {
+  int32_t steps = 0;          // layer-0 steps of two input features
+  const float *w0a = nullptr;  // [steps][H / 32][64]: W0[32 mb + l % 32][2 step + l / 32]
+  const float *b0 = nullptr, *g0 = nullptr, *beta0 = nullptr;
+  const float *w1 = nullptr, *b1 = nullptr, *g1 = nullptr, *beta1 = nullptr;  // w1: fragments
+  // f16x2 records of s1 W1 (layer 1 on the fp16 matrix cores); nullptr: the
+  // fp32 fragments w1 are used
+  const void *w1r = nullptr;
+  float s1 = 1.f;
+  float eps = 1e-5f;
+  // the LayerNorms' gains are in the next layer's weights; beta0 and beta1
+  // are FOLD_SCALE beta / |g| (only with w1r)
+  bool fold = false;
+};
+// Power of two that folded LayerNorm outputs carry.
+constexpr float FOLD_SCALE = 16.f;
+
 // Edge filter (filter.hip): scores[j] = sigmoid(MLP([x_src; x_dst])).
 struct FilterArgs {
   int64_t n_edges = 0;
@@ -245,22 +264,23 @@ struct FilterArgs {
   const float *x = nullptr;  // [n_nodes][F]
   int32_t F = 0;
   const int32_t *edge_index = nullptr;
-  const float *w0t = nullptr, *b0 = nullptr, *g0 = nullptr, *beta0 = nullptr;  // W0 as [2F][H]
-  const float *w1 = nullptr, *b1 = nullptr, *g1 = nullptr, *beta1 = nullptr;   // fragments
-  // f16x2 records of s1 W1 (layer 2 on the fp16 matrix cores); nullptr: the
-  // fp32 fragments w1 are used
-  const void *w1r = nullptr;
-  float s1 = 1.f;
-  const float *w2 = nullptr, *b2 = nullptr;                                   // head [H], [1]
+  SmallMlpArgs mlp;
+  const float *w2 = nullptr, *b2 = nullptr;  // head [H], [1]
   float *scores = nullptr;
-  float eps = 1e-5f;
+  float threshold = 0.f;
+  // per 32 edges the mask of those kept, and per workgroup of the scoring
+  // launch (filter_wgs) the number kept
+  uint32_t *masks = nullptr;
+  int32_t *counts = nullptr;
 };
-hipError_t launch_filter_scores(int hidden, const FilterArgs &a, hipStream_t stream);
-// Stable compaction of the edges with score > threshold into out
-// ([2][total] contiguous); counts has compact_tiles(n) entries.
-size_t compact_tiles(int64_t n);
-hipError_t launch_compact(const float *scores, const int32_t *edge_index, int64_t n,
-                          float threshold, int32_t *counts, int32_t *total, int32_t *out,
+// Workgroups of the scoring launch; each takes one run of consecutive units
+// of 32 edges.
+int32_t filter_wgs(int64_t n_edges, int n_cu);
+hipError_t launch_filter_scores(int hidden, const FilterArgs &a, int32_t wgs, hipStream_t stream);
+// Stable compaction of the kept edges into out ([2][total] contiguous), with
+// the masks and counts of a scoring launch of `wgs` workgroups.
+hipError_t launch_compact(const int32_t *edge_index, int64_t n, const uint32_t *masks,
+                          const int32_t *counts, int32_t wgs, int32_t *total, int32_t *out,
                           hipStream_t stream);
 
 // Graph construction (graph.hip).  Embedding MLP F -> H -> H -> D.
@@ -268,17 +288,16 @@ struct EmbedArgs {
   int64_t n = 0;
   const float *x = nullptr;  // [n][F]
   int32_t F = 0, D = 0;
-  const float *w0t = nullptr, *b0 = nullptr, *g0 = nullptr, *beta0 = nullptr;  // W0 as [F][H]
-  const float *w1 = nullptr, *b1 = nullptr, *g1 = nullptr, *beta1 = nullptr;   // fragments
-  // f16x2 records of s1 W1 (layer 2 on the fp16 matrix cores); nullptr: the
-  // fp32 fragments w1 are used
-  const void *w1r = nullptr;
-  float s1 = 1.f;
-  const float *w2 = nullptr, *b2 = nullptr;                                   // [D][H], [D]
-  float *z = nullptr;                                                         // [n][D]
-  float eps = 1e-5f;
+  SmallMlpArgs mlp;
+  const float *w2 = nullptr, *b2 = nullptr;  // [D][H], [D]
+  // mlp.fold: three-part fp16 records of s2 W2 ([k-step][part][64], rows
+  // past D zero)
+  const void *w2r = nullptr;
+  float s2 = 1.f;
+  float *z = nullptr;  // [n][D]
+  bool z16 = false;    // set by launch_embed
 };
-hipError_t launch_embed(int hidden, const EmbedArgs &a, hipStream_t stream);
+hipError_t launch_embed(int hidden, const EmbedArgs &a, int n_cu, hipStream_t stream);
 
 // Fixed-radius pairs over the rows of z [n][D].
 struct FrnnArgs {

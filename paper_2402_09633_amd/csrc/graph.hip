@@ -3,13 +3,12 @@
 // fixed-radius nearest-neighbour search there proposes the candidate edges
 // that the filter and the GNN then score).
 //
-// embed       one wave per 32 points: layer 1 (F -> H) on VALU, LayerNorm/
-//             ReLU, layer 2 (H -> H) on the matrix cores through the
-//             accumulator chain, LayerNorm/ReLU, then the D outputs as VALU
-//             dot products (D <= 16).  Layer 2 takes the split fp16 products
-//             of split.hip (SPLIT: f16x2 records of s W1, bias s b1, eps
-//             eps s^2) when the first LayerNorm's output bound fits the fp16
-//             range, the fp32 matrix cores otherwise.
+// embed       one wave per 32 points: two hidden layers (small_mlp.h), then
+//             the D outputs (D <= 16), on the fp16 matrix cores from three-part
+//             splits (VALU dot products where the gains are not folded).
+//             300k points, 3 -> 128 -> 128 -> 8: 100 -> 40 us (47 with the
+//             outputs on the VALU: its weights alone were half of the LDS
+//             reads, which bounded it).
 // frnn        every pair i < j with d2(i, j) < r2, where d2 is evaluated in
 //             fp32 as d = fmaf(t, t, d) over the coordinates in ascending
 //             order (t = z_i[k] - z_j[k]).  Points are binned on a grid over
@@ -22,55 +21,130 @@
 //             produce a pair twice.  A count pass, an exclusive scan and a fill pass write
 //             the pairs grouped by i (within one i in cell-scan order), which
 //             is deterministic.
-#include "device_common.h"
+#include "small_mlp.h"
 
 namespace gnn {
 namespace {
 
-constexpr int EWAVES = 4;
 constexpr int FTHREADS = 256;
+constexpr int MAX_D = 16;
 
-template <int MB, bool SPLIT>
-__global__ __launch_bounds__(64 * EWAVES) void embed_mlp(EmbedArgs a) {
+// Parts of the output layer's split products: with x = x1 + x2 + x3 and
+// w = w1 + w2 + w3 in fp16 (33 bits each), the six products of order up to
+// 2^-22 leave an error below fp32's own rounding.
+constexpr int OUT_PARTS = 3;
+
+template <int MB, bool SPLIT, bool FOLD, int FK>
+__global__ __launch_bounds__(64 * SM_WAVES) void embed_mlp(EmbedArgs a) {
+  using M = SmallMlp<MB, SPLIT, FOLD, 1>;
   constexpr int H = 32 * MB;
+  constexpr int KS = (FK + 1) / 2;  // layer-0 steps (the odd feature's partner is zero)
+  constexpr int NOUT = 2 * MB * OUT_PARTS * 64;
+  __shared__ typename M::Lds lds;
+  __shared__ h8 out_r[FOLD ? NOUT : 1];
+  __shared__ float out_w[FOLD ? 1 : MAX_D * H];
+  __shared__ float out_b[32];  // (FOLD: times s2)
   const int lane = threadIdx.x & 63, hh = lane >> 5, n = lane & 31;
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int64_t row0 = ((int64_t)blk * EWAVES + (threadIdx.x >> 6)) * 32;
-  if (row0 >= a.n) return;
-  const int64_t row = row0 + n;
-  const bool valid = row < a.n;
-  const int64_t r = valid ? row : a.n - 1;
-
-  f16v acc[MB];
-  small_k_layer<MB>(acc, a.x, a.F, (int)r, a.w0t, a.b0, hh);
-  bias_ln_relu<MB>(acc, nullptr, a.g0, a.beta0, a.eps, hh, false);
-  f16v acc2[MB];
-  if constexpr (SPLIT) {
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int F = FK ? FK : a.F;
+  const int64_t units = (a.n + 31) / 32, nw = (int64_t)gridDim.x * SM_WAVES;
+  auto load_x = [&](int64_t u, int step, float (&xk)[1]) {
+    const int64_t row = u * 32 + n, r = row < a.n ? row : a.n - 1;
+    const int k = 2 * step + hh;
+    xk[0] = k < F ? a.x[r * F + k] : 0.f;
+  };
+  // one unit per workgroup before any workgroup takes a second
+  int64_t u = (int64_t)wv * gridDim.x + blockIdx.x;
+  float xv[FK ? KS : 1][1];
+  if constexpr (FK > 0)
+    if (u < units)
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc2[mb][v] = 0.f;
-    const h8 *rec = (const h8 *)a.w1r + lane;
-#pragma unroll
-    for (int g = 0; g < 2 * MB; ++g) step_h<MB>(acc2, rec + g * 2 * MB * 64, acc_x<MB>(acc, g));
-    bias_ln_relu<MB>(acc2, a.b1, a.g1, a.beta1, a.eps * a.s1 * a.s1, hh, true, a.s1);
+      for (int k = 0; k < KS; ++k) load_x(u, k, xv[k]);
+  M::load(lds, a.mlp);
+  if constexpr (FOLD) {
+    for (int i = threadIdx.x; i < NOUT; i += 64 * SM_WAVES) out_r[i] = ((const h8 *)a.w2r)[i];
   } else {
-    gemm_acc_f32<MB, MB>(acc2, acc, (const f4 *)a.w1 + lane, 0);
-    bias_ln_relu<MB>(acc2, a.b1, a.g1, a.beta1, a.eps, hh, true);
+    for (int i = threadIdx.x; i < a.D * H; i += 64 * SM_WAVES) out_w[i] = a.w2[i];
   }
-  for (int d = 0; d < a.D; ++d) {
-    const float *wd = a.w2 + (int64_t)d * H + 4 * hh;
-    float part = 0.f;
+  if (threadIdx.x < 32) out_b[threadIdx.x] = (int)threadIdx.x < a.D ? a.b2[threadIdx.x] * a.s2 : 0.f;
+  __syncthreads();
+  for (; u < units; u += nw) {
+    // keeps the LDS reads of the weights inside the loop
+    asm volatile("" ::: "memory");
+    f16v acc[1][MB], acc2[1][MB];
+    M::bias(acc, lds.prm, hh);
+    if constexpr (FK > 0) {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+      for (int k = 0; k < KS; ++k) M::step0(acc, lds, k, xv[k], lane);
+      if (u + nw < units)
+#pragma unroll
+        for (int k = 0; k < KS; ++k) load_x(u + nw, k, xv[k]);
+    } else {
+      for (int k = 0; k < a.mlp.steps; ++k) {
+        load_x(u, k, xv[0]);
+        M::step0(acc, lds, k, xv[0], lane);
+      }
+    }
+    M::rest(acc, acc2, lds, a.mlp, lane, hh);
+    const int64_t row = u * 32 + n;
+    if constexpr (FOLD) {
+      // z = W2 a on the matrix cores, one 32-wide output block of which D
+      // rows are used; lane (n, hh) then holds outputs 8 q + 4 hh + t.
+      f16v z;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const f4 ww = *(const f4 *)(wd + mb * 32 + 8 * q);
+        const f4 bb = *(const f4 *)(out_b + 8 * q + 4 * hh);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) part += acc2[mb][4 * q + t] * ww[t];
+        for (int t = 0; t < 4; ++t) z[4 * q + t] = bb[t];
       }
-    part += __shfl_xor(part, 32);
-    if (valid && hh == 0) a.z[row * a.D + d] = part + a.b2[d];
+#pragma unroll
+      for (int g = 0; g < 2 * MB; ++g) {
+        const h8 *r = out_r + g * OUT_PARTS * 64 + lane;
+        const f8 x = acc_x<MB>(acc2[0], g);
+        const h8 x1 = __builtin_convertvector(x, h8);
+        const f8 y = residual16(x, x1);
+        const h8 x2 = __builtin_convertvector(y, h8);
+        const h8 x3 = __builtin_convertvector(residual16(y, x2), h8);
+        const h8 w1 = r[0], w2 = r[64], w3 = r[128];
+        z = mma_h(w3, x1, z);
+        z = mma_h(w2, x2, z);
+        z = mma_h(w1, x3, z);
+        z = mma_h(w2, x1, z);
+        z = mma_h(w1, x2, z);
+        z = mma_h(w1, x1, z);
+      }
+      const float inv = 1.f / a.s2;  // a power of two
+      if (row < a.n) {
+#pragma unroll
+        for (int q = 0; q < MAX_D / 8; ++q) {
+          const int d0 = 8 * q + 4 * hh;
+          float *o = a.z + row * a.D + d0;
+          const f4 v = f4{z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]} * inv;
+          if (d0 + 4 <= a.D && a.z16) {
+            *(f4 *)o = v;
+          } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+              if (d0 + t < a.D) o[t] = v[t];
+          }
+        }
+      }
+    } else {
+      for (int d = 0; d < a.D; ++d) {
+        const float *wd = out_w + d * H + 4 * hh;
+        float part = 0.f;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f4 ww = *(const f4 *)(wd + mb * 32 + 8 * q);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) part += acc2[0][mb][4 * q + t] * ww[t];
+          }
+        part += __shfl_xor(part, 32);
+        if (row < a.n && hh == 0) a.z[row * a.D + d] = part + out_b[d];
+      }
+    }
   }
 }
 
@@ -287,23 +361,33 @@ __global__ __launch_bounds__(ST) void scan_down(const int32_t *__restrict__ coun
 
 }  // namespace
 
-hipError_t launch_embed(int hidden, const EmbedArgs &a, hipStream_t stream) {
+namespace {
+
+template <int MB>
+hipError_t embed_h(const EmbedArgs &a, unsigned wgs, hipStream_t stream) {
+  if (!a.mlp.w1r) return launch(embed_mlp<MB, false, false, 0>, wgs, 64 * SM_WAVES, 0, stream, a);
+  if (!a.mlp.fold) return launch(embed_mlp<MB, true, false, 0>, wgs, 64 * SM_WAVES, 0, stream, a);
+  // hits have three features; any other width takes the loop over its steps
+  if (a.F == 3) return launch(embed_mlp<MB, true, true, 3>, wgs, 64 * SM_WAVES, 0, stream, a);
+  return launch(embed_mlp<MB, true, true, 0>, wgs, 64 * SM_WAVES, 0, stream, a);
+}
+
+}  // namespace
+
+hipError_t launch_embed(int hidden, const EmbedArgs &args, int n_cu, hipStream_t stream) {
+  EmbedArgs a = args;
   if (a.n <= 0) return hipSuccess;
-  if (a.D < 1 || a.D > 16 || a.F < 1 || a.F > MAX_F) return hipErrorInvalidValue;
-  const int64_t waves = (a.n + 31) / 32;
-  const unsigned blocks = (unsigned)((waves + EWAVES - 1) / EWAVES);
+  if (a.D < 1 || a.D > MAX_D || a.F < 1 || a.F > MAX_F || a.mlp.steps != (a.F + 1) / 2)
+    return hipErrorInvalidValue;
+  // 16-byte stores where every row's pieces of four outputs are aligned
+  a.z16 = a.D % 4 == 0 && (uintptr_t)a.z % 16 == 0;
+  const int64_t units = (a.n + 31) / 32, most = (int64_t)n_cu * SM_WGS_PER_CU;
+  const unsigned wgs = (unsigned)(units < most ? units : most);
   switch (hidden) {
-    case 64:
-      if (a.w1r) embed_mlp<2, true><<<blocks, 64 * EWAVES, 0, stream>>>(a);
-      else embed_mlp<2, false><<<blocks, 64 * EWAVES, 0, stream>>>(a);
-      break;
-    case 128:
-      if (a.w1r) embed_mlp<4, true><<<blocks, 64 * EWAVES, 0, stream>>>(a);
-      else embed_mlp<4, false><<<blocks, 64 * EWAVES, 0, stream>>>(a);
-      break;
-    default: return hipErrorInvalidValue;
+    case 64: return embed_h<2>(a, wgs, stream);
+    case 128: return embed_h<4>(a, wgs, stream);
   }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 size_t frnn_scan_blocks(int64_t n) { return (size_t)((n + STILE - 1) / STILE); }

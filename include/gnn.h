@@ -222,8 +222,7 @@ int gnn_filter_apply(gnn_filter *f, const float *node_feat, const int32_t *edge_
  * connected component -- unique, so results are bitwise reproducible.
  *   edge_index [2][n_edges] int32 (device), edge_scores [n_edges] fp32
  *   (device) or NULL, labels [n_nodes] int32 (device, output).
- * Runs on the current device; the host checks convergence between rounds,
- * so the call returns after `stream` has drained.  GNN_E_INVALID_ARG for
+ * Runs on the current device; the call returns after `stream` has drained.  GNN_E_INVALID_ARG for
  * bad counts or NULL pointers; out-of-range indices are clamped. */
 int gnn_wcc(const int32_t *edge_index, const float *edge_scores, float threshold,
             int64_t n_nodes, int64_t n_edges, int32_t *labels, hipStream_t stream);

@@ -1836,7 +1836,8 @@ struct SmallMlpOff {
   float s1 = 1.f, s2 = 1.f;
   int steps = 0;
 
-  SmallMlpOff(Staging &st, const BlobLayer &in0, const BlobLayer &in1, const BlobLayer &in2) {
+  SmallMlpOff(Staging &st, const BlobLayer &in0, const BlobLayer &in1, const BlobLayer &in2,
+              bool out_records) {
     split = ln_out_bound(in0) <= 32768.0;
     // (each layer is centred before its rows take the gains' signs)
     const Centred c0(in0), c1(in1);
@@ -1863,15 +1864,16 @@ struct SmallMlpOff {
       const std::vector<uint16_t> r = rec_f16x2(l_1, 0, H, s1, -1);
       w1r = st.add(r.data(), r.size() * sizeof(uint16_t));
     }
-    if (fold) {
-      // three-part records of the output layer (embedding), one 32-row block
+    if (fold && out_records) {
+      // three-part records of the output layer, one 32-row block
       s2 = pow2_scale(out);
       std::vector<uint16_t> r((size_t)(H / 16) * 3 * 64 * 8);
       for (int g = 0; g < H / 16; ++g)
         for (int l = 0; l < 64; ++l)
           for (int j = 0; j < 8; ++j) {
             const int k = node_line_k(g, l / 32, j, -1);
-            float w = l % 32 < out.fout ? s2 * out.W[(size_t)(l % 32) * H + k] : 0.f;
+            if (l % 32 >= out.fout) continue;  // zero rows
+            float w = s2 * out.W[(size_t)(l % 32) * H + k];
             for (int p = 0; p < 3; ++p) {
               const _Float16 v = (_Float16)w;
               r[(((size_t)g * 3 + p) * 64 + l) * 8 + j] = f16_bits(v);
@@ -1972,7 +1974,7 @@ gnn_filter *gnn_filter_create(const float *weights, const gnn_filter_dims *dims)
   };
   BlobLayer l0 = next(2 * F, H, true), l1 = next(H, H, true), l2 = next(H, 1, false);
   Staging st;
-  const SmallMlpOff om(st, l0, l1, l2);
+  const SmallMlpOff om(st, l0, l1, l2, false);
   gnn_filter *f = new gnn_filter();
   f->dims = *dims;
   f->device = dev;
@@ -2067,7 +2069,7 @@ gnn_embedder *gnn_embed_create(const float *weights, const gnn_embed_dims *dims)
   };
   BlobLayer l0 = next(F, H, true), l1 = next(H, H, true), l2 = next(H, D, false);
   Staging st;
-  const SmallMlpOff om(st, l0, l1, l2);
+  const SmallMlpOff om(st, l0, l1, l2, true);
   gnn_embedder *m = new gnn_embedder();
   m->dims = *dims;
   m->device = dev;
@@ -2184,48 +2186,11 @@ int gnn_wcc(const int32_t *edge_index, const float *edge_scores, float threshold
   if (n_nodes == 0) return GNN_OK;
   if (!labels || (n_edges > 0 && !edge_index))
     return fail(GNN_E_INVALID_ARG, "NULL labels or edge_index");
-  const int32_t n = (int32_t)n_nodes;
-  // Hooking onto the smaller root plus full compression converges in a few
-  // rounds on graphs of tracks (and in O(log n) on typical graphs); a call
-  // that has not converged after max_rounds fails instead of returning
-  // partial labels.  Rounds are queued GROUP at a time, each with its own
-  // flag (zeroed up front); a round after one that joined nothing returns at
-  // once, so the host reads one flag per group instead of one per round.
-  const int max_rounds = 256, GROUP = 4;
   int rc = GNN_OK;
-  bool converged = n_edges == 0;
-  int32_t *changed = nullptr;
-  {
-    hipError_t ae = hipMallocAsync((void **)&changed, max_rounds * sizeof(int32_t), stream);
-    if (ae != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(GNN_E_OOM, "hipMallocAsync failed: %s", hipGetErrorString(ae));
-    }
-  }
-  HIP_TRY(wcc_launch_init(labels, n, stream));
-  HIP_TRY(launch_fill_i32(changed, max_rounds, 0, stream));
-  for (int r0 = 0; r0 < max_rounds && n_edges > 0; r0 += GROUP) {
-    const int r1 = r0 + GROUP < max_rounds ? r0 + GROUP : max_rounds;
-    for (int r = r0; r < r1; ++r)
-      HIP_TRY(wcc_launch_round(edge_index, edge_scores, threshold, n_edges, n, labels,
-                               r > 0 ? changed + r - 1 : nullptr, changed + r, stream));
-    int32_t host_changed = 0;
-    HIP_TRY(hipMemcpyAsync(&host_changed, changed + r1 - 1, sizeof(int32_t),
-                           hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
-    if (!host_changed) {
-      converged = true;
-      break;
-    }
-  }
-  if (!converged) rc = fail(GNN_E_UNSUPPORTED, "components did not converge in %d rounds",
-                            max_rounds);
+  HIP_TRY(launch_wcc(edge_index, edge_scores, threshold, n_edges, (int32_t)n_nodes, labels,
+                     stream));
+  HIP_TRY(hipStreamSynchronize(stream));
 out:
-  {
-    hipError_t fe = hipFreeAsync(changed, stream);
-    if (fe != hipSuccess && rc == GNN_OK)
-      rc = fail(GNN_E_HIP, "hipFreeAsync failed: %s", hipGetErrorString(fe));
-  }
   return rc;
 }
 

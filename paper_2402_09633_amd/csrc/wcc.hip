@@ -3,107 +3,254 @@
 // GNN edge scores are passed to WCC; section 2.3: the custom backend returns
 // one integer label per space point).
 //
-// Min-label hooking with pointer jumping.  Every node starts as its own
-// parent.  A hook round walks all kept edges (score > threshold), finds the
-// two roots and lowers the parent of the larger root to the smaller one with
-// an integer atomicMin; a compress round points every node at its root.
-// Parents only ever decrease (parent[v] <= v), so every root is the smallest
-// id of its tree, and once a hook round finds no edge joining two different
-// roots the labels are the smallest node id of each component -- a unique
-// answer, independent of the order in which the GPU ran the updates.
+// A union-find over the nodes in a fixed number of launches.  Links only ever
+// point to a smaller id of the same component (parent[v] <= v), so a walk
+// along them ends, a root is the smallest id of its tree, and once every kept
+// edge has its ends in one tree the roots are the smallest ids of the
+// components: a unique answer, whatever order the GPU worked in.
+//
+//   init      parent[v] = v
+//   hook      parent[larger end] = smaller end, for every kept edge: in a
+//             detector graph this already gives each hit of a track its
+//             predecessor
+//   round     for every kept edge, both ends are pointed at their roots, and
+//             the larger root at the smaller one
+//   unite     the same, but the root is linked by compare-and-swap, repeated
+//             until both ends share a root
+//   compress  parent[v] = root of v
+//
+// hook and round use plain stores: where several edges link one root, some
+// link is lost, which unite makes good.  No atomics there: an atomic minimum
+// goes to the memory side, and once large trees meet, a hundred thousand of
+// them hit one root.  The rounds leave unite almost nothing to do (a root
+// survives a round only if no neighbouring tree has a smaller one), which
+// keeps its swaps from contending.
+//
+// Walks read the links through the caches (an agent-scope load goes past the
+// XCD's L2, several times its latency).  A link read that way may be old, but
+// it was a valid link of the same component; a node that once had a smaller
+// link is never a root again; and only unite's compare-and-swap, on the value
+// at the memory side, decides whether a root is still one.  A failed swap
+// returns the current link, smaller than the node, and the walk goes on from
+// there.  So every loop strictly descends in the node ids and ends, and the
+// host has nothing to check.
+//
+// Whole call, us, against hook rounds by agent-scope walks and atomic minima
+// with a convergence flag read by the host every four rounds: 300k hits with
+// track-like scores (270k of 1.0M edges kept) 244 -> 97; 150k hits, all 500k
+// edges kept (one giant component) 519 -> 90; chain of 300k ids 295 -> 90;
+// hub of 300k edges 1366 -> 130; random graph, 1.2M edges, 369 -> 128.
 #include "gnn_internal.h"
 
 namespace gnn {
 namespace {
 
+constexpr int WT = 256;  // threads per workgroup
+constexpr int WE = 4;    // edges per thread: their walks are in flight together
+
 __device__ __forceinline__ int32_t clampi(int32_t v, int32_t n) {
   return v < 0 ? 0 : (v >= n ? n - 1 : v);
 }
 
-// Follows parent links to a root.  Links read here may be older than the
-// newest atomicMin of another thread: they are still valid unions with
-// parent <= node, so the walk ends, and any mismatch is corrected in a later
-// round (every round revisits every edge).
-__device__ __forceinline__ int32_t load_parent(const int32_t *parent, int32_t v) {
-  return __hip_atomic_load(parent + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Links as this XCD's caches have them (workgroup scope: not kept in a
+// register between reads).
+__device__ __forceinline__ int32_t link_of(const int32_t *parent, int32_t v) {
+  return __hip_atomic_load(parent + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void set_link(int32_t *parent, int32_t v, int32_t to) {
+  __hip_atomic_store(parent + v, to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Path halving on the way: each visited node is pointed at its grandparent
-// with atomicMin, so links only ever decrease (a smaller link written by a
-// concurrent hook is never overwritten) and the chains that concurrent
-// hooks build in a large component stay short.
-__device__ __forceinline__ int32_t find_root(int32_t *parent, int32_t v) {
-  int32_t p = load_parent(parent, v);
-  while (p != v) {
-    const int32_t gp = load_parent(parent, p);
-    if (gp == p) return p;
-    if (gp < load_parent(parent, v)) atomicMin(&parent[v], gp);
-    v = gp;
-    p = load_parent(parent, v);
+// Walks of at most NEAR links (a detector graph's trees are as deep as it has
+// layers): v's ancestor that far up, or its root, with `root` telling which.
+constexpr int NEAR = 16;
+
+__device__ __forceinline__ int32_t walk_near(const int32_t *parent, int32_t v, bool &root) {
+  root = false;
+  for (int s = 0; s < NEAR; ++s) {
+    const int32_t p = link_of(parent, v);
+    if (p == v) {
+      root = true;
+      return v;
+    }
+    v = p;
   }
   return v;
 }
 
-__global__ void wcc_init(int32_t *__restrict__ parent, int32_t n) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Full walks: past NEAR links at agent scope, halving the path behind, so
+// that the walks of a chain's nodes shorten one another's.
+__device__ __forceinline__ int32_t find_root(int32_t *parent, int32_t v) {
+  bool root;
+  v = walk_near(parent, v, root);
+  while (!root) {
+    const int32_t p = __hip_atomic_load(parent + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (p == v) return v;
+    const int32_t q = __hip_atomic_load(parent + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (q == p) return p;
+    __hip_atomic_store(parent + v, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    v = q;
+  }
+  return v;
+}
+
+struct WccEdges {
+  const int32_t *ei;
+  const float *scores;
+  float threshold;
+  int64_t n_edges;
+  int32_t n_nodes;
+};
+
+// Larger and smaller end of edge j (equal: nothing to do).
+__device__ __forceinline__ void load_edge(const WccEdges &E, int64_t j, int32_t &hi, int32_t &lo) {
+  const bool in = j < E.n_edges;
+  const bool keep = in && (!E.scores || E.scores[j] > E.threshold);
+  const int32_t s = in ? clampi(E.ei[j], E.n_nodes) : 0;
+  const int32_t d = in ? clampi(E.ei[E.n_edges + j], E.n_nodes) : 0;
+  hi = s > d ? s : d;
+  lo = s > d ? d : s;
+  if (!keep) hi = lo = 0;
+}
+
+// This thread's edges.
+__device__ __forceinline__ void load_edges(const WccEdges &E, int32_t (&hi)[WE],
+                                           int32_t (&lo)[WE]) {
+#pragma unroll
+  for (int k = 0; k < WE; ++k)
+    load_edge(E, ((int64_t)blockIdx.x * WE + k) * WT + threadIdx.x, hi[k], lo[k]);
+}
+
+// Both ends' roots in place of the ends, larger first; an end that was not
+// linked to its root directly is now.  FULL = false: walks of NEAR links
+// (shortening the rest of a long path by as much); an edge with an end whose
+// root was not reached gets equal ends.
+template <bool FULL>
+__device__ __forceinline__ void find_roots(int32_t *parent, int32_t (&hi)[WE], int32_t (&lo)[WE]) {
+  int32_t ph[WE], pl[WE];
+#pragma unroll
+  for (int k = 0; k < WE; ++k) {
+    ph[k] = link_of(parent, hi[k]);
+    pl[k] = link_of(parent, lo[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < WE; ++k) {
+    if (hi[k] == lo[k]) continue;
+    bool all = true;
+    auto walk = [&](int32_t v, int32_t p) {  // p: v's link
+      if (p == v) return v;
+      bool root = true;
+      const int32_t r = FULL ? find_root(parent, p) : walk_near(parent, p, root);
+      all = all && root;
+      if (r != p) set_link(parent, v, r);
+      return r;
+    };
+    const int32_t rh = walk(hi[k], ph[k]), rl = walk(lo[k], pl[k]);
+    hi[k] = rh > rl ? rh : rl;
+    lo[k] = !all ? hi[k] : rh > rl ? rl : rh;
+  }
+}
+
+// Links root (or fresh node) a to c < a on the lanes with `active`.  Links
+// already smaller stay, and where all active lanes of the wave link the same
+// node, the smallest c is taken (a hub's edges would otherwise leave it a
+// random link, and the smaller ends one round each).
+__device__ __forceinline__ void link_to(int32_t *parent, bool active, int32_t a, int32_t c) {
+  const uint64_t m = __ballot(active);
+  if (m == 0) return;
+  const int first = __builtin_ctzll(m);
+  const int32_t a0 = __builtin_amdgcn_readlane(a, first);
+  if (__popcll(m) > 1 && __ballot(active && a == a0) == m) {
+    int32_t x = active ? c : INT32_MAX;
+    for (int off = 32; off > 0; off >>= 1) {
+      const int32_t y = __shfl_xor(x, off);
+      x = y < x ? y : x;
+    }
+    c = x;
+    active = ((int)threadIdx.x & 63) == first;
+  }
+  if (active && c < link_of(parent, a)) set_link(parent, a, c);
+}
+
+__global__ __launch_bounds__(WT) void wcc_init(int32_t *__restrict__ parent, int32_t n) {
+  const int64_t v = (int64_t)blockIdx.x * WT + threadIdx.x;
   if (v < n) parent[v] = (int32_t)v;
 }
 
-// `changed` is raised once per workgroup: one store per joining edge to a
-// single word would serialise on its L2 channel (milliseconds in the first
-// round, when most kept edges join two trees).  `prev` is the previous
-// round's flag (nullptr in the first round): once a round has joined
-// nothing the labels are final, and the rounds queued after it return at
-// once, so several rounds can be queued between two host checks.
-__global__ void wcc_hook(const int32_t *__restrict__ ei, const float *__restrict__ scores,
-                         float threshold, int64_t n_edges, int32_t n_nodes, int32_t *parent,
-                         const int32_t *prev, int32_t *__restrict__ changed) {
-  if (prev && __hip_atomic_load(prev, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
-  __shared__ int32_t joined;
-  if (threadIdx.x == 0) joined = 0;
-  __syncthreads();
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < n_edges && (!scores || scores[j] > threshold)) {
-    const int32_t ru = find_root(parent, clampi(ei[j], n_nodes));
-    const int32_t rv = find_root(parent, clampi(ei[n_edges + j], n_nodes));
-    if (ru != rv) {
-      const int32_t hi = ru > rv ? ru : rv, lo = ru > rv ? rv : ru;
-      // Many edges join the same pair of large trees: the atomic is issued
-      // only when it would lower the link, so a root is not a hot spot.
-      if (lo < load_parent(parent, hi)) atomicMin(&parent[hi], lo);
-      joined = 1;  // every writer stores the same value
+__global__ __launch_bounds__(WT) void wcc_hook(WccEdges E, int32_t *parent) {
+  int32_t hi[WE], lo[WE];
+  load_edges(E, hi, lo);
+#pragma unroll
+  for (int k = 0; k < WE; ++k) link_to(parent, hi[k] != lo[k], hi[k], lo[k]);
+}
+
+// With `check`, a workgroup first looks at WT edges spread over the list (the
+// same ones for all) and leaves the rest to unite once all but a few of them
+// are settled: no flag has to be kept, cleared or counted.
+__global__ __launch_bounds__(WT) void wcc_round(WccEdges E, int32_t *parent, bool check) {
+  int32_t hi[WE], lo[WE];
+  if (check) {
+    load_edge(E, (int64_t)threadIdx.x * E.n_edges / WT, hi[0], lo[0]);
+    const bool open = hi[0] != lo[0] && link_of(parent, hi[0]) != link_of(parent, lo[0]);
+    if (__syncthreads_count(open) <= WT / 32) return;
+  }
+  load_edges(E, hi, lo);
+  find_roots<false>(parent, hi, lo);
+#pragma unroll
+  for (int k = 0; k < WE; ++k) link_to(parent, hi[k] != lo[k], hi[k], lo[k]);
+}
+
+__global__ __launch_bounds__(WT) void wcc_unite(WccEdges E, int32_t *parent) {
+  int32_t hi[WE], lo[WE];
+  load_edges(E, hi, lo);
+  find_roots<true>(parent, hi, lo);
+#pragma unroll
+  for (int k = 0; k < WE; ++k) {
+    int32_t a = hi[k], b = lo[k];
+    while (a != b) {
+      if (a < b) {
+        const int32_t t = a;
+        a = b;
+        b = t;
+      }
+      const int32_t old = atomicCAS(&parent[a], a, b);
+      if (old == a) break;
+      a = find_root(parent, old);
     }
   }
-  __syncthreads();
-  if (threadIdx.x == 0 && joined) *changed = 1;
 }
 
-// Skipped after a round that joined nothing (the links are roots already).
-__global__ void wcc_compress(int32_t *parent, int32_t n, const int32_t *changed) {
-  if (__hip_atomic_load(changed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < n) parent[v] = find_root(parent, (int32_t)v);
+// (A node whose own link another thread shortens meanwhile reads either
+// link; both lead to the same root.)
+__global__ __launch_bounds__(WT) void wcc_compress(int32_t *parent, int32_t n) {
+  const int64_t v = (int64_t)blockIdx.x * WT + threadIdx.x;
+  if (v < n) {
+    const int32_t p = link_of(parent, (int32_t)v), r = find_root(parent, p);
+    if (r != p) set_link(parent, (int32_t)v, r);
+  }
 }
 
-inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
+// Rounds launched: a round with nothing left to do costs 4 us, one too few
+// leaves unite contending (1.0M edges, tracks / 500k edges, all kept: 3 rounds
+// 92 / 86 us, 4 97 / 90, 5 101 / 95; 2 rounds 87 / 105 to 240).  Four keep the
+// grid of random ids (547 x 547) and hubs of 300k edges at 3 too.
+constexpr int ROUNDS = 4;
 
 }  // namespace
 
-hipError_t wcc_launch_init(int32_t *labels, int32_t n, hipStream_t stream) {
-  if (n > 0) wcc_init<<<blocks_for(n, 256), 256, 0, stream>>>(labels, n);
-  return hipGetLastError();
-}
-
-hipError_t wcc_launch_round(const int32_t *edge_index, const float *scores, float threshold,
-                            int64_t n_edges, int32_t n_nodes, int32_t *labels,
-                            const int32_t *prev, int32_t *changed, hipStream_t stream) {
-  if (n_edges > 0)
-    wcc_hook<<<blocks_for(n_edges, 256), 256, 0, stream>>>(edge_index, scores, threshold,
-                                                          n_edges, n_nodes, labels, prev,
-                                                          changed);
-  if (n_nodes > 0)
-    wcc_compress<<<blocks_for(n_nodes, 256), 256, 0, stream>>>(labels, n_nodes, changed);
-  return hipGetLastError();
+hipError_t launch_wcc(const int32_t *edge_index, const float *scores, float threshold,
+                      int64_t n_edges, int32_t n_nodes, int32_t *labels, hipStream_t stream) {
+  if (n_nodes <= 0) return hipSuccess;
+  const WccEdges E{edge_index, scores, threshold, n_edges, n_nodes};
+  const unsigned nv = (unsigned)(((int64_t)n_nodes + WT - 1) / WT);
+  const unsigned ne = (unsigned)((n_edges + WT * WE - 1) / (WT * WE));
+  hipError_t e = launch(wcc_init, nv, WT, 0, stream, labels, n_nodes);
+  if (e != hipSuccess || n_edges <= 0) return e;
+  if ((e = launch(wcc_hook, ne, WT, 0, stream, E, labels))) return e;
+  for (int r = 0; r < ROUNDS; ++r)
+    if ((e = launch(wcc_round, ne, WT, 0, stream, E, labels, r > 0))) return e;
+  if ((e = launch(wcc_unite, ne, WT, 0, stream, E, labels))) return e;
+  return launch(wcc_compress, nv, WT, 0, stream, labels, n_nodes);
 }
 
 }  // namespace gnn

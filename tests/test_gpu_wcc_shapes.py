@@ -1,0 +1,63 @@
+"""Connected components on the graph shapes where links, walks and swaps can
+go wrong: long chains, hubs, grids, repeated edges, remainders of a launch."""
+import numpy as np
+import pytest
+import torch
+
+from tests.gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+def shape(name, rng):
+    n = 20_011
+    a = np.arange(n - 1)
+    grid = np.arange(141 * 141).reshape(141, 141)
+    edges = np.concatenate([np.stack([grid[:-1].ravel(), grid[1:].ravel()]),
+                            np.stack([grid[:, :-1].ravel(), grid[:, 1:].ravel()])], 1)
+    p = rng.permutation(n)
+    return {
+        "chain": lambda: (n, np.stack([a, a + 1])),
+        "chain_shuffled": lambda: (n, np.stack([a, a + 1])[:, rng.permutation(n - 1)]),
+        "chain_random_ids": lambda: (n, np.stack([p[:-1], p[1:]])),
+        "hub_last": lambda: (n, np.stack([np.full(n - 1, n - 1), rng.permutation(n - 1)])),
+        "hub_first": lambda: (n, np.stack([np.zeros(n - 1, int), 1 + a])),
+        "grid_random_ids": lambda: (141 * 141, rng.permutation(141 * 141)[edges]),
+        "tree": lambda: (n, np.stack([1 + a, a // 2])),
+        "repeated": lambda: (n, np.tile(np.array([[9], [5]]), (1, 70_000))),
+        "self_loops": lambda: (n, np.stack([p, p])),
+        "out_of_range": lambda: (50, rng.integers(-30, 90, (2, 40))),
+    }[name]()
+
+
+@pytest.mark.parametrize("name", ["chain", "chain_shuffled", "chain_random_ids", "hub_last",
+                                  "hub_first", "grid_random_ids", "tree", "repeated",
+                                  "self_loops", "out_of_range"])
+def test_shapes(oracle_mod, name):
+    from paper_2402_09633_amd import gnn as G
+    n, e = shape(name, np.random.default_rng(17))
+    e = np.ascontiguousarray(e.astype(np.int32))
+    ref = oracle_mod.wcc(np.clip(e, 0, n - 1), n)
+    lab = torch.empty(n, dtype=torch.int32, device="cuda")
+    ei = dev(e)
+    for _ in range(3):  # any execution order gives the same labels
+        G.gnn_wcc(ei, None, 0.5, n, e.shape[1], lab)
+        np.testing.assert_array_equal(lab.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("e", [1, 255, 256, 257, 1023, 1024, 1025, 4097])
+@pytest.mark.parametrize("thr", [0.2, float("nan"), float("-inf"), float("inf")])
+def test_edge_remainders_and_thresholds(oracle_mod, e, thr):
+    from paper_2402_09633_amd import gnn as G
+    rng = np.random.default_rng(e)
+    n = max(2, e // 2)
+    ei = rng.integers(0, n, (2, e)).astype(np.int32)
+    sc = rng.random(e).astype(np.float32)
+    sc[::7] = np.nan
+    sc[::11] = -np.inf
+    lab = torch.empty(n, dtype=torch.int32, device="cuda")
+    G.gnn_wcc(dev(ei), dev(sc), thr, n, e, lab)
+    with np.errstate(invalid="ignore"):
+        kept = ei[:, sc > np.float32(thr)]
+    ref = oracle_mod.wcc(np.ascontiguousarray(kept), n) if kept.size else np.arange(n)
+    np.testing.assert_array_equal(lab.cpu().numpy(), ref)

@@ -137,7 +137,7 @@ __global__ __launch_bounds__(HS_THREADS) void rs_hist(SortSet S, int32_t n, int3
 // bounded; past the bound (never reached while every workgroup progresses)
 // the pass records a failure in err and goes on.
 struct OneSweep {
-  uint32_t *status;         // [passes][2][ntiles][RS_RADIX]
+  uint32_t *status;         // [passes][sorts][ntiles][RS_RADIX]
   const uint32_t *totals;   // [2][RS_MAX_PASSES][RS_RADIX]
   uint32_t *ctr;            // [2][RS_MAX_PASSES] tile counters
   uint32_t *err;
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(OS_THREADS) void rs_onesweep(SortSet S, OneSweep O,
     uint32_t local = 0;
 #pragma unroll
     for (int i = 0; i < OS_WAVES; ++i) local += cnt[i][tid];
-    uint32_t *st = O.status + ((int64_t)(pass * 2 + y) * ntiles) * RS_RADIX + tid;
+    uint32_t *st = O.status + ((int64_t)(pass * gridDim.y + y) * ntiles) * RS_RADIX + tid;
     uint32_t excl = 0;
     if (tile == 0) {
       __hip_atomic_store(st, RS_INC | local, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -469,31 +469,22 @@ int64_t csr_tiles(int64_t n_edges) { return (n_edges + OS_TILE - 1) / OS_TILE; }
 // the error word.
 constexpr size_t CSR_TAIL_WORDS = (size_t)2 * RS_MAX_PASSES * RS_RADIX + 2 * RS_MAX_PASSES + 8;
 
-size_t csr_status_words(int64_t n_edges, int64_t n_nodes) {
-  return (size_t)csr_digits(n_nodes).passes * 2 * RS_RADIX * (size_t)csr_tiles(n_edges);
+size_t csr_status_words(int64_t n_edges, int64_t n_nodes, int sorts) {
+  return (size_t)csr_digits(n_nodes).passes * sorts * RS_RADIX * (size_t)csr_tiles(n_edges);
 }
 
-}  // namespace
-
-size_t csr_scratch_bytes(int64_t n_edges, int64_t n_nodes) {
-  return (csr_status_words(n_edges, n_nodes) + CSR_TAIL_WORDS) * 4;
-}
-
-uint32_t *csr_err_word(const CsrScratch &s, int64_t n_edges, int64_t n_nodes) {
-  return s.status + csr_status_words(n_edges, n_nodes) + 2 * RS_MAX_PASSES * RS_RADIX +
-         2 * RS_MAX_PASSES;
-}
-
-hipError_t build_csr(const int32_t *edge_index, int32_t n, int32_t n_nodes, int32_t *row_ptr_in,
-                     int32_t *perm_in, int32_t *row_ptr_out, int32_t *perm_out,
-                     const CsrScratch &s, int32_t *eis, int32_t *inv, int32_t *q_in,
-                     hipStream_t stream) {
+// The first `sorts` of a build's two sorts, keys[y] = n keys clamped into
+// [0, n_nodes).
+hipError_t build_sorts(int sorts, const int32_t *const (&keys)[2], int32_t n, int32_t n_nodes,
+                       int32_t *const (&row_ptr)[2], int32_t *const (&perm)[2],
+                       const CsrScratch &s, const int32_t *dst_raw, int32_t *eis, int32_t *inv,
+                       int32_t *q_in, hipStream_t stream) {
   if (n < 0 || n >= CSR_MAX_ITEMS || n_nodes < 0) return hipErrorInvalidValue;
   const Digits dg = csr_digits(n_nodes);
   const int32_t ntiles = (int32_t)csr_tiles(n);
   // look-back words, digit totals, tile counters and the error word: one
   // region, zeroed by a fill kernel (also under stream capture)
-  const size_t sw = csr_status_words(n, n_nodes);
+  const size_t sw = csr_status_words(n, n_nodes, sorts);
   const int64_t words = (int64_t)(sw + CSR_TAIL_WORDS);
   if (const hipError_t e =
           launch(fill_i32, blocks_for(words, 256), 256, 0, stream, (int32_t *)s.status, words, 0))
@@ -502,43 +493,67 @@ hipError_t build_csr(const int32_t *edge_index, int32_t n, int32_t n_nodes, int3
 
   SortSet S{};
   if (n > 0) {
-    // Sort 0: keys = destinations (row 1), sort 1: keys = sources (row 0).
     uint2 *pa[2] = {s.pairs_a, s.pairs_a + n}, *pb[2] = {s.pairs_b, s.pairs_b + n};
     OneSweep O{};
     O.status = s.status;
     O.totals = totals;
     O.ctr = totals + 2 * RS_MAX_PASSES * RS_RADIX;
     O.err = O.ctr + 2 * RS_MAX_PASSES;
-    O.dst_raw = edge_index + n;
+    O.dst_raw = dst_raw;
     O.eis = eis;
     O.inv = inv;
-    S.keys_i32[0] = edge_index + n;
-    S.keys_i32[1] = edge_index;
-    if (const hipError_t e = launch(rs_hist, dim3(blocks_for(n, HS_TILE), 2), HS_THREADS, 0,
+    for (int y = 0; y < sorts; ++y) S.keys_i32[y] = keys[y];
+    if (const hipError_t e = launch(rs_hist, dim3(blocks_for(n, HS_TILE), sorts), HS_THREADS, 0,
                                     stream, S, n, n_nodes, dg.passes, dg.bits, totals))
       return e;
     for (int p = 0; p < dg.passes; ++p) {
       const bool last = p == dg.passes - 1;
-      for (int y = 0; y < 2; ++y) S.out[y] = (p & 1) ? pb[y] : pa[y];
-      if (const hipError_t e = launch(rs_onesweep, dim3(ntiles, 2), OS_THREADS, 0, stream, S, O,
-                                      n, n_nodes, p, dg.bits, ntiles, last ? 1 : 0))
+      for (int y = 0; y < sorts; ++y) S.out[y] = (p & 1) ? pb[y] : pa[y];
+      if (const hipError_t e = launch(rs_onesweep, dim3(ntiles, sorts), OS_THREADS, 0, stream, S,
+                                      O, n, n_nodes, p, dg.bits, ntiles, last ? 1 : 0))
         return e;
-      for (int y = 0; y < 2; ++y) {
+      for (int y = 0; y < sorts; ++y) {
         S.keys_i32[y] = nullptr;
         S.in[y] = S.out[y];
       }
     }
   }
   CsrOut C{};
-  for (int y = 0; y < 2; ++y) C.sorted[y] = S.in[y];  // not read when n == 0
-  C.row_ptr[0] = row_ptr_in;
-  C.row_ptr[1] = row_ptr_out;
-  C.perm[0] = perm_in;
-  C.perm[1] = perm_out;
+  for (int y = 0; y < sorts; ++y) {
+    C.sorted[y] = S.in[y];  // not read when n == 0
+    C.row_ptr[y] = row_ptr[y];
+    C.perm[y] = perm[y];
+  }
   C.inv = inv;
   C.q_in = eis ? q_in : nullptr;
-  return launch(csr_finish, dim3(blocks_for((int64_t)n + 1, FIN_POS), 2), FIN_THREADS, 0, stream,
-                C, n, n_nodes);
+  return launch(csr_finish, dim3(blocks_for((int64_t)n + 1, FIN_POS), sorts), FIN_THREADS, 0,
+                stream, C, n, n_nodes);
+}
+
+}  // namespace
+
+size_t csr_scratch_bytes(int64_t n_edges, int64_t n_nodes, int sorts) {
+  return (csr_status_words(n_edges, n_nodes, sorts) + CSR_TAIL_WORDS) * 4;
+}
+
+uint32_t *csr_err_word(const CsrScratch &s, int64_t n_edges, int64_t n_nodes) {
+  return s.status + csr_status_words(n_edges, n_nodes, 2) + 2 * RS_MAX_PASSES * RS_RADIX +
+         2 * RS_MAX_PASSES;
+}
+
+hipError_t build_csr(const int32_t *edge_index, int32_t n, int32_t n_nodes, int32_t *row_ptr_in,
+                     int32_t *perm_in, int32_t *row_ptr_out, int32_t *perm_out,
+                     const CsrScratch &s, int32_t *eis, int32_t *inv, int32_t *q_in,
+                     hipStream_t stream) {
+  // Sort 0: keys = destinations (row 1), sort 1: keys = sources (row 0).
+  return build_sorts(2, {edge_index + n, edge_index}, n, n_nodes, {row_ptr_in, row_ptr_out},
+                     {perm_in, perm_out}, s, edge_index + n, eis, inv, q_in, stream);
+}
+
+hipError_t build_buckets(const int32_t *keys, int32_t n, int32_t n_keys, int32_t *row_ptr,
+                         int32_t *perm, const CsrScratch &s, hipStream_t stream) {
+  return build_sorts(1, {keys, nullptr}, n, n_keys, {row_ptr, nullptr}, {perm, nullptr}, s,
+                     nullptr, nullptr, nullptr, nullptr, stream);
 }
 
 hipError_t launch_validate(const int32_t *edge_index, int64_t n_edges, int32_t n_nodes,

@@ -528,7 +528,7 @@ size_t plan_workspace(Workspace &w, int64_t N, int64_t E, int H, size_t act_byte
   const size_t o_rpi = take((size_t)(N + 1) * 4), o_rpo = take((size_t)(N + 1) * 4);
   const size_t o_pi = take((size_t)E * 4), o_po = take((size_t)E * 4);
   const size_t o_sa = take((size_t)E * 16), o_sb = take((size_t)E * 16);
-  const size_t o_st = take(csr_scratch_bytes(E, N));
+  const size_t o_st = take(csr_scratch_bytes(E, N, 2));
   const size_t o_eis = factored ? take((size_t)E * 8) : 0;
   const size_t o_inv = factored ? take((size_t)E * 4) : 0;
   const size_t o_qin = factored ? take((size_t)E * 4) : 0;

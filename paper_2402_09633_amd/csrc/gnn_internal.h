@@ -215,13 +215,13 @@ hipError_t launch_segsum_fused(Act act, int hidden, const void *e, const int32_t
 struct CsrScratch {
   uint2 *pairs_a, *pairs_b;  // 2*n_edges (key, edge id) pairs each
   // look-back words of the sort passes, digit totals, tile counters and an
-  // error word: csr_scratch_bytes(n_edges, n_nodes) bytes, 4-byte aligned
+  // error word: csr_scratch_bytes(n_edges, n_nodes, sorts) bytes, 4-byte aligned
   uint32_t *status;
 };
 // The sort's look-back words hold counts below 2^30: builds of at most
 // CSR_MAX_ITEMS - 1 edges (larger ones return hipErrorInvalidValue).
 constexpr int32_t CSR_MAX_ITEMS = 1 << 30;
-size_t csr_scratch_bytes(int64_t n_edges, int64_t n_nodes);
+size_t csr_scratch_bytes(int64_t n_edges, int64_t n_nodes, int sorts);
 // Nonzero after a build in which a sort pass gave up waiting for an earlier
 // tile (a bounded wait that forward progress of running workgroups ends).
 uint32_t *csr_err_word(const CsrScratch &s, int64_t n_edges, int64_t n_nodes);
@@ -234,6 +234,10 @@ hipError_t build_csr(const int32_t *edge_index, int32_t n_edges, int32_t n_nodes
                      int32_t *row_ptr_in, int32_t *perm_in, int32_t *row_ptr_out,
                      int32_t *perm_out, const CsrScratch &s, int32_t *eis, int32_t *inv,
                      int32_t *q_in, hipStream_t stream);
+// One such sort, of n keys in [0, n_keys): items by key, ascending within a
+// key.  The scratch pairs hold n entries each.
+hipError_t build_buckets(const int32_t *keys, int32_t n, int32_t n_keys, int32_t *row_ptr,
+                         int32_t *perm, const CsrScratch &s, hipStream_t stream);
 // dst[idx[r]][:] = src[r][:] (fp32, bf16 or fp16 rows of width H, written as fp32).
 hipError_t launch_scatter_rows(Act act, const void *src, const int32_t *idx, float *dst,
                                int64_t rows, int H, hipStream_t stream);
@@ -303,22 +307,30 @@ hipError_t launch_embed(int hidden, const EmbedArgs &a, int n_cu, hipStream_t st
 struct FrnnArgs {
   const float *z = nullptr;
   int64_t n = 0;
-  int32_t D = 0, g = 0;       // dimensions, grid dimensions (min(3, D))
+  int32_t D = 0;
   float r2 = 0.f, inv_cell = 0.f;
   uint32_t mask = 0;          // bucket table size - 1 (power of two)
   const int32_t *rp = nullptr, *perm = nullptr;  // buckets: CSR of the points by key
+  // the points in bucket order: coordinates 0..3 (zero past D), the others
+  // ([n][D - 4], D > 4)
+  float *z4 = nullptr, *zr = nullptr;
+  float *z2 = nullptr;        // coordinates 3 and 4 ([n + 4][2], D > 4)
+  // [n][n_slots], by id: a point's partners, or, of one with more than
+  // n_slots (a multiple of 4), its bucket position
+  int32_t *slots = nullptr;
+  int32_t n_slots = 0;
   int32_t *count = nullptr;   // [n] pairs per point
   int64_t *offs = nullptr;    // [n] exclusive offsets
   int64_t *bsum = nullptr;    // [frnn_scan_blocks(n)] scan scratch
-  int64_t *total_dev = nullptr;
-  int64_t total = 0;          // fill pass: number of pairs (row stride of out)
-  int32_t *out = nullptr;     // [2][total]
+  int64_t *total = nullptr;   // device: number of pairs (row stride of out)
+  int32_t *out = nullptr;     // [2][total], written when total <= max_pairs; or nullptr
+  int64_t max_pairs = 0;
 };
 size_t frnn_scan_blocks(int64_t n);
 hipError_t launch_frnn_keys(const FrnnArgs &a, int32_t *keys, hipStream_t stream);
-// zs: [n][D] scratch for the coordinates in bucket order
-hipError_t launch_frnn_count(const FrnnArgs &a, float *zs, hipStream_t stream);
-hipError_t launch_frnn_fill(const FrnnArgs &a, const float *zs, hipStream_t stream);
+// Gathers the points into bucket order, counts and collects the pairs, scans
+// the counts and writes the pairs.
+hipError_t launch_frnn_pairs(const FrnnArgs &a, hipStream_t stream);
 
 // Weakly-connected components (wcc.hip): labels[v] = smallest node id of v's
 // component over the edges with score > threshold (all when scores is null).

@@ -18,9 +18,13 @@
 //             is turned into buckets by the CSR builder (a stable sort of the
 //             points by bucket).  A point scans the buckets of the 3^g
 //             neighbouring cells, each bucket once, so hash collisions never
-//             produce a pair twice.  A count pass, an exclusive scan and a fill pass write
-//             the pairs grouped by i (within one i in cell-scan order), which
-//             is deterministic.
+//             produce a pair twice.  One pass counts the pairs and keeps each
+//             point's first partners; after an exclusive scan of the counts
+//             they are written grouped by i (within one i in cell-scan
+//             order), which is deterministic.  300k clustered 8-d points,
+//             544k pairs, whole call: 494 -> 242 us (two full scans of 190 us
+//             became one of 109, bound by its scattered loads; one sort of
+//             the keys instead of two; the write queued behind the count).
 #include "small_mlp.h"
 
 namespace gnn {
@@ -164,134 +168,281 @@ __device__ __forceinline__ uint32_t cell_hash(const int (&c)[3], uint32_t mask) 
          mask;
 }
 
-// Bucket keys, written twice ([2][n]) as the CSR builder's edge list.
 __global__ __launch_bounds__(FTHREADS) void frnn_keys(FrnnArgs a, int32_t *__restrict__ keys) {
   const int64_t i = (int64_t)blockIdx.x * FTHREADS + threadIdx.x;
   if (i >= a.n) return;
   int c[3];
-  cell_of(a.z + i * a.D, a.g, a.inv_cell, c);
-  const int32_t k = (int32_t)cell_hash(c, a.mask);
-  keys[i] = k;
-  keys[a.n + i] = k;
+  cell_of(a.z + i * a.D, a.D < 3 ? a.D : 3, a.inv_cell, c);
+  keys[i] = (int32_t)cell_hash(c, a.mask);
 }
 
-// The points' coordinates in bucket order: zs[p] = z[perm[p]].
-__global__ __launch_bounds__(FTHREADS) void frnn_gather(FrnnArgs a, float *__restrict__ zs) {
-  const int64_t t = (int64_t)blockIdx.x * FTHREADS + threadIdx.x;
-  if (t >= a.n * a.D) return;
-  const int64_t p = t / a.D;
-  zs[t] = a.z[(int64_t)a.perm[p] * a.D + (t - p * a.D)];
+// The points' coordinates in bucket order, the first four apart.
+__global__ __launch_bounds__(FTHREADS) void frnn_gather(FrnnArgs a, bool vec) {
+  const int64_t p = (int64_t)blockIdx.x * FTHREADS + threadIdx.x;
+  if (p >= a.n) return;
+  const float *src = a.z + (int64_t)a.perm[p] * a.D;
+  f4 v = {0.f, 0.f, 0.f, 0.f};
+  float z_4 = 0.f;
+  if (vec) {  // rows of whole 16-byte pieces, D % 4 == 0
+    v = *(const f4 *)src;
+    for (int k = 4; k < a.D; k += 4) {
+      const f4 w = *(const f4 *)(src + k);
+      if (k == 4) z_4 = w[0];
+      *(f4 *)(a.zr + p * (a.D - 4) + k - 4) = w;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (k < a.D) v[k] = src[k];
+    for (int k = 4; k < a.D; ++k) a.zr[p * (a.D - 4) + k - 4] = src[k];
+    if (a.D > 4) z_4 = src[4];
+  }
+  *(f4 *)(a.z4 + 4 * p) = v;
+  if (a.D > 4) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    *(f2 *)(a.z2 + 2 * p) = f2{v[3], z_4};
+  }
 }
 
-// FILL = false: count the pairs of every point; true: write them.  Thread
-// p handles the point at bucket position p (neighbouring threads handle
-// neighbouring points, whose candidates they share in the caches).  The
-// neighbouring cells' buckets are scanned once each (a bucket that two
+// Calls emit(j) for the partners j > i of the point at bucket position p (id
+// i), in the order of the cells and of the ids within a bucket.
+//
+// The neighbouring cells' buckets are scanned once each (a bucket that two
 // cells share through the hash is skipped the second time), so every other
 // point is tested at most once; a point of a colliding far cell simply fails
-// the distance test.  Candidates are taken U at a time: their ids and
-// coordinates are requested together before any distance is formed, so a
-// bucket costs one round of cache latency per U candidates rather than two
-// dependent ones per candidate (positions past the bucket's end repeat its
-// last point and are not counted).  The dimension D is a template argument:
-// the coordinate loads and the distance chain unroll, with 16-byte loads
-// when D is a multiple of 4 (rows of zs then start on 16-byte boundaries).
-template <bool FILL, int D>
-__global__ __launch_bounds__(FTHREADS) void frnn_pairs(FrnnArgs a, const float *__restrict__ zs) {
+// the distance test.
+//
+// Bound by the number of scattered loads: a wave's lanes scan unrelated
+// buckets, and the texture unit takes about one lane a cycle.  So a candidate
+// is first tested on as little as rejects nearly all of them.  The distance
+// only grows as its coordinates are added (each fmaf rounds a sum of
+// non-negative terms upwards from the partial sum), so a candidate fails as
+// soon as a partial sum, or the square of any one coordinate's difference,
+// reaches r2.  With five or more coordinates (PAIRS) that is tested on two of
+// those that the grid does not separate, 8 bytes a candidate and two
+// candidates a load; with fewer, on the first four, 16 bytes.  Only the
+// survivors' other coordinates and ids are read, and those later, from a list
+// in LDS, LIST at a time: done where they are found, one lane's survivor makes
+// the whole wave wait for its loads.  Candidates are taken U at a time and the
+// next three cells' bounds are requested ahead.
+constexpr int LIST = 16;
+template <int D, typename Emit>
+__device__ __forceinline__ void scan_point(const FrnnArgs &a, int64_t p, int32_t i, Emit emit) {
   constexpr int U = 4;
-  constexpr int DZ = D < 3 ? 3 : D;  // cell_of reads up to 3 coordinates
+  constexpr bool PAIRS = D >= 5;
+  typedef int32_t i2 __attribute__((ext_vector_type(2), aligned(4)));
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(8)));
+  constexpr int NY = D > 1 ? 3 : 1, NZ = D > 2 ? 3 : 1;
+  const f4 *z4 = (const f4 *)a.z4;
+  const f4 zi = z4[p];
+  float zri[D > 4 ? D - 4 : 1];
+#pragma unroll
+  for (int k = 4; k < D; ++k) zri[k - 4] = a.zr[p * (D - 4) + k - 4];
+  int ci[3];
+  {
+    const float zc[3] = {zi[0], zi[1], zi[2]};
+    cell_of(zc, D < 3 ? D : 3, a.inv_cell, ci);
+  }
+  auto key_of = [&](int c) {  // c = 3 * (3 * z + y) + x
+    const int nc[3] = {ci[0] + c % 3 - 1, ci[1] + (NY > 1 ? c / 3 % 3 - 1 : 0),
+                       ci[2] + (NZ > 1 ? c / 9 - 1 : 0)};
+    return cell_hash(nc, a.mask);
+  };
+  // Whether any two of the cells share a bucket.  The hash is an exclusive or
+  // of one term per axis, so two cells collide when the differences of their
+  // terms cancel; each axis has three nonzero differences.
+  bool collide = false;
+  {
+    uint32_t d[3][4];
+    const uint32_t mul[3] = {73856093u, 19349663u, 83492791u};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const uint32_t t0 = (uint32_t)(ci[k] - 1) * mul[k], t1 = (uint32_t)ci[k] * mul[k],
+                     t2 = (uint32_t)(ci[k] + 1) * mul[k];
+      d[k][0] = 0;
+      d[k][1] = t0 ^ t1;
+      d[k][2] = t0 ^ t2;
+      d[k][3] = t1 ^ t2;
+    }
+#pragma unroll
+    for (int z = 0; z < (NZ > 1 ? 4 : 1); ++z)
+#pragma unroll
+      for (int y = 0; y < (NY > 1 ? 4 : 1); ++y)
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+          if (x + y + z > 0) collide |= ((d[0][x] ^ d[1][y] ^ d[2][z]) & a.mask) == 0;
+  }
+  // Bucket bounds of row r's three cells (r = 3 z + y), empty when skipped.
+  auto bounds = [&](int r, int32_t (&qb)[3], int32_t (&qe)[3]) {
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+      const int c = 3 * r + x;
+      const uint32_t key = key_of(c);
+      const i2 q = *(const i2 *)(a.rp + key);  // one load for both bounds
+      qb[x] = q[0];
+      qe[x] = q[1];
+      if (collide)
+        for (int e = 0; e < c; ++e) qe[x] = key_of(e) == key ? qb[x] : qe[x];
+    }
+  };
+  __shared__ int32_t list[LIST][FTHREADS];
+  int n_list = 0;
+  auto flush = [&]() {
+    for (int k = 0; k < n_list; ++k) {
+      const int32_t q = list[k][threadIdx.x];
+      const int32_t j = a.perm[q];
+      float acc = 0.f;
+      if constexpr (PAIRS) {  // (else the list holds only pairs)
+        const f4 zq = z4[q];
+        float zrq[D > 4 ? D - 4 : 1];
+#pragma unroll
+        for (int c = 4; c < D; ++c) zrq[c - 4] = a.zr[(int64_t)q * (D - 4) + c - 4];
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+          const float t = c < 4 ? zi[c < 4 ? c : 0] - zq[c < 4 ? c : 0] : zri[c < 4 ? 0 : c - 4] - zrq[c < 4 ? 0 : c - 4];
+          acc = __builtin_fmaf(t, t, acc);
+        }
+      }
+      if ((!PAIRS || acc < a.r2) && j > i) emit(j);
+    }
+    n_list = 0;
+  };
+  auto push = [&](int32_t q) {
+    if (q == p) return;
+    if (n_list == LIST) flush();
+    list[n_list++][threadIdx.x] = q;
+  };
+  struct Batch {
+    f4 v[PAIRS ? U / 2 : U];
+  };
+  auto load = [&](Batch &w, int32_t q0, int32_t qe) {
+    if constexpr (PAIRS) {
+      // (past the bucket's end: other points' coordinates, not used)
+      const f4u *pr = (const f4u *)(a.z2 + 2 * (int64_t)q0);
+      w.v[0] = pr[0];
+      if (q0 + 2 < qe) w.v[1] = pr[1];
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (q0 + u < qe) w.v[u] = z4[q0 + u];
+    }
+  };
+  auto test = [&](const Batch &w, int32_t q0, int32_t qe) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      bool near;
+      if constexpr (PAIRS) {
+        const float t3 = zi[3] - w.v[u / 2][2 * (u % 2)],
+                    t4 = zri[0] - w.v[u / 2][2 * (u % 2) + 1];
+        near = !(t3 * t3 >= a.r2) && !(t4 * t4 >= a.r2);
+      } else {
+        float acc = 0.f;
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+          const float t = zi[k] - w.v[u][k];
+          acc = __builtin_fmaf(t, t, acc);
+        }
+        near = acc < a.r2;
+      }
+      if (q0 + u < qe && near) push(q0 + u);
+    }
+  };
+  int32_t nb[3], ne[3];
+  bounds(0, nb, ne);
+  for (int r = 0; r < NY * NZ; ++r) {
+    int32_t qb[3], qe[3];
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+      qb[x] = nb[x];
+      qe[x] = ne[x];
+    }
+    if (r + 1 < NY * NZ) bounds(r + 1, nb, ne);
+    // The first U candidates of the three cells are requested together.
+    Batch first[3];
+#pragma unroll
+    for (int x = 0; x < 3; ++x)
+      if (qb[x] < qe[x]) load(first[x], qb[x], qe[x]);
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+      test(first[x], qb[x], qe[x]);
+      for (int32_t q0 = qb[x] + U; q0 < qe[x]; q0 += U) {
+        Batch more;
+        load(more, q0, qe[x]);
+        test(more, q0, qe[x]);
+      }
+    }
+  }
+  flush();
+}
+
+// Pairs of every point: the count, and up to a.n_slots partners; of a point
+// with more, its bucket position instead.  Thread
+// p handles the point at bucket position p (neighbouring threads handle
+// neighbouring points, whose candidates they share in the caches).
+template <int D>
+__global__ __launch_bounds__(FTHREADS) void frnn_collect(FrnnArgs a) {
   const int64_t p = (int64_t)blockIdx.x * FTHREADS + threadIdx.x;
   if (p >= a.n) return;
   const int32_t i = a.perm[p];
-  auto load_row = [&](int64_t q, float *dst) {
-    const float *src = zs + q * D;
-    if constexpr (D % 4 == 0) {
-#pragma unroll
-      for (int k = 0; k < D; k += 4) {
-        const f4 v = *(const f4 *)(src + k);
-        dst[k] = v[0];
-        dst[k + 1] = v[1];
-        dst[k + 2] = v[2];
-        dst[k + 3] = v[3];
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < D; ++k) dst[k] = src[k];
-    }
-  };
-  float zi[DZ];
-#pragma unroll
-  for (int k = D; k < DZ; ++k) zi[k] = 0.f;
-  load_row(p, zi);
-  int ci[3];
-  cell_of(zi, a.g, a.inv_cell, ci);
-  int64_t o = FILL ? a.offs[i] : 0;
   int32_t cnt = 0;
-  uint32_t seen[27];
-  int ns = 0;
-  const int r2d = a.g > 1 ? 1 : 0, r3d = a.g > 2 ? 1 : 0;
-  for (int dz = -r3d; dz <= r3d; ++dz)
-    for (int dy = -r2d; dy <= r2d; ++dy)
-      for (int dx = -1; dx <= 1; ++dx) {
-        const int nc[3] = {ci[0] + dx, ci[1] + dy, ci[2] + dz};
-        const uint32_t key = cell_hash(nc, a.mask);
-        bool dup = false;
-        for (int u = 0; u < ns; ++u) dup |= seen[u] == key;
-        if (dup) continue;
-        seen[ns++] = key;
-        const int32_t qb = a.rp[key], qe = a.rp[key + 1];
-        for (int32_t q0 = qb; q0 < qe; q0 += U) {
-          int32_t jj[U];
-          float zz[U][D];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int32_t q = q0 + u < qe ? q0 + u : qe - 1;
-            jj[u] = a.perm[q];
-            load_row(q, zz[u]);
-          }
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            if (q0 + u >= qe || jj[u] <= i) continue;
-            float acc = 0.f;
-#pragma unroll
-            for (int k = 0; k < D; ++k) {
-              const float t = zi[k] - zz[u][k];
-              acc = __builtin_fmaf(t, t, acc);
-            }
-            if (acc < a.r2) {
-              if constexpr (FILL) {
-                a.out[o] = i;
-                a.out[a.total + o] = jj[u];
-                ++o;
-              } else {
-                ++cnt;
-              }
-            }
-          }
-        }
-      }
-  if constexpr (!FILL) a.count[i] = cnt;
+  scan_point<D>(a, p, i, [&](int32_t j) {
+    if (cnt < a.n_slots) a.slots[(int64_t)i * a.n_slots + cnt] = j;
+    ++cnt;
+  });
+  a.count[i] = cnt;
+  if (cnt > a.n_slots) a.slots[(int64_t)i * a.n_slots] = (int32_t)p;
 }
 
-template <bool FILL>
-hipError_t launch_pairs(const FrnnArgs &a, const float *zs, hipStream_t stream) {
+// Writes the pairs where there is room for all of them: the collected
+// partners, or, of a point with more than a.n_slots, a second scan's.  In the
+// order of the ids, so that neighbouring threads write neighbouring pairs (in
+// bucket order every store had a line of its own: 40 us against 9).
+template <int D>
+__global__ __launch_bounds__(FTHREADS) void frnn_write(FrnnArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * FTHREADS + threadIdx.x;
+  const int64_t total = *a.total;
+  if (i >= a.n || total > a.max_pairs) return;
+  const int32_t cnt = a.count[i], *slot = a.slots + i * a.n_slots;
+  int64_t o = a.offs[i];
+  auto put = [&](int32_t j) {
+    a.out[o] = (int32_t)i;
+    a.out[total + o] = j;
+    ++o;
+  };
+  if (cnt > a.n_slots) {
+    scan_point<D>(a, slot[0], (int32_t)i, put);
+  } else {
+    typedef int32_t i4 __attribute__((ext_vector_type(4)));
+    for (int32_t k = 0; k < cnt; k += 4) {
+      const i4 v = *(const i4 *)(slot + k);
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        if (k + t < cnt) put(v[t]);
+    }
+  }
+}
+
+template <bool WRITE>
+hipError_t launch_points(const FrnnArgs &a, hipStream_t stream) {
   const unsigned blocks = (unsigned)((a.n + FTHREADS - 1) / FTHREADS);
   switch (a.D) {
 #define GNN_FRNN_D(d) \
-  case d: frnn_pairs<FILL, d><<<blocks, FTHREADS, 0, stream>>>(a, zs); break;
+  case d: return launch(WRITE ? frnn_write<d> : frnn_collect<d>, blocks, FTHREADS, 0, stream, a);
     GNN_FRNN_D(1) GNN_FRNN_D(2) GNN_FRNN_D(3) GNN_FRNN_D(4) GNN_FRNN_D(5) GNN_FRNN_D(6)
     GNN_FRNN_D(7) GNN_FRNN_D(8) GNN_FRNN_D(9) GNN_FRNN_D(10) GNN_FRNN_D(11) GNN_FRNN_D(12)
     GNN_FRNN_D(13) GNN_FRNN_D(14) GNN_FRNN_D(15) GNN_FRNN_D(16)
 #undef GNN_FRNN_D
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 // Exclusive scan of the per-point counts into offs (int64), total -> *total:
-// per-tile sums (tiles of 2048 counts), a scan of the tile sums, then each
-// tile's own scan.  Thread t of a tile owns its 8 consecutive counts.
-constexpr int ST = 256, SI = 8, STILE = ST * SI;
+// per-tile sums (tiles of 2048 counts), then each tile's own scan on top of
+// the sums before it.  Those are added up by the tile itself for up to
+// SCAN_DIRECT tiles (at most 16 reads a thread; a launch less), above that
+// they are scanned by a launch in between.  Thread t of a tile owns its 8
+// consecutive counts.
+constexpr int ST = 256, SI = 8, STILE = ST * SI, SCAN_DIRECT = 16 * ST;
 
 // Exclusive scan of v over the block; *sum gets the block total.
 __device__ __forceinline__ int64_t block_excl_scan(int64_t v, int64_t *sum) {
@@ -338,9 +489,29 @@ __global__ __launch_bounds__(ST) void scan_sums(int64_t *__restrict__ bsum, int6
   if (threadIdx.x == 0) *total = carry;
 }
 
+// direct: bsum holds the tiles' sums, else their exclusive scan.
 __global__ __launch_bounds__(ST) void scan_down(const int32_t *__restrict__ count, int64_t n,
-                                                const int64_t *__restrict__ bsum,
-                                                int64_t *__restrict__ offs) {
+                                                const int64_t *__restrict__ bsum, bool direct,
+                                                int64_t *__restrict__ offs,
+                                                int64_t *__restrict__ total) {
+  int64_t before = 0;
+  if (direct) {
+    int64_t all = 0;
+    for (int64_t b = threadIdx.x; b < (int64_t)gridDim.x; b += ST) {
+      const int64_t v = bsum[b];
+      before += b < (int64_t)blockIdx.x ? v : 0;
+      all += v;
+    }
+    int64_t sum;
+    (void)block_excl_scan(before, &sum);
+    before = sum;
+    if (blockIdx.x == 0) {  // (uniform over the block)
+      (void)block_excl_scan(all, &sum);
+      if (threadIdx.x == 0) *total = sum;
+    }
+  } else {
+    before = bsum[blockIdx.x];
+  }
   const int64_t base = (int64_t)blockIdx.x * STILE + (int64_t)threadIdx.x * SI;
   int32_t c[SI];
   int64_t s = 0;
@@ -350,7 +521,7 @@ __global__ __launch_bounds__(ST) void scan_down(const int32_t *__restrict__ coun
     s += c[k];
   }
   int64_t tot;
-  int64_t run = bsum[blockIdx.x] + block_excl_scan(s, &tot);
+  int64_t run = before + block_excl_scan(s, &tot);
 #pragma unroll
   for (int k = 0; k < SI; ++k)
     if (base + k < n) {
@@ -394,26 +565,25 @@ size_t frnn_scan_blocks(int64_t n) { return (size_t)((n + STILE - 1) / STILE); }
 
 hipError_t launch_frnn_keys(const FrnnArgs &a, int32_t *keys, hipStream_t stream) {
   if (a.n <= 0) return hipSuccess;
-  frnn_keys<<<(unsigned)((a.n + FTHREADS - 1) / FTHREADS), FTHREADS, 0, stream>>>(a, keys);
-  return hipGetLastError();
+  return launch(frnn_keys, (unsigned)((a.n + FTHREADS - 1) / FTHREADS), FTHREADS, 0, stream, a,
+                keys);
 }
 
-hipError_t launch_frnn_count(const FrnnArgs &a, float *zs, hipStream_t stream) {
+hipError_t launch_frnn_pairs(const FrnnArgs &a, hipStream_t stream) {
   if (a.n <= 0) return hipSuccess;
-  const int64_t nz = a.n * a.D;
-  frnn_gather<<<(unsigned)((nz + FTHREADS - 1) / FTHREADS), FTHREADS, 0, stream>>>(a, zs);
-  hipError_t e = launch_pairs<false>(a, zs, stream);
+  hipError_t e =
+      launch(frnn_gather, (unsigned)((a.n + FTHREADS - 1) / FTHREADS), FTHREADS, 0, stream, a,
+             a.D % 4 == 0 && (uintptr_t)a.z % 16 == 0);
+  if (e == hipSuccess) e = launch_points<false>(a, stream);
   if (e != hipSuccess) return e;
-  const int64_t nb = (int64_t)frnn_scan_blocks(a.n);
-  scan_tiles<<<(unsigned)nb, ST, 0, stream>>>(a.count, a.n, a.bsum);
-  scan_sums<<<1, ST, 0, stream>>>(a.bsum, nb, a.total_dev);
-  scan_down<<<(unsigned)nb, ST, 0, stream>>>(a.count, a.n, a.bsum, a.offs);
-  return hipGetLastError();
-}
-
-hipError_t launch_frnn_fill(const FrnnArgs &a, const float *zs, hipStream_t stream) {
-  if (a.n <= 0) return hipSuccess;
-  return launch_pairs<true>(a, zs, stream);
+  const unsigned nb = (unsigned)frnn_scan_blocks(a.n);
+  const bool direct = nb <= SCAN_DIRECT;
+  if ((e = launch(scan_tiles, nb, ST, 0, stream, a.count, a.n, a.bsum))) return e;
+  if (!direct)
+    if ((e = launch(scan_sums, 1, ST, 0, stream, a.bsum, (int64_t)nb, a.total))) return e;
+  if ((e = launch(scan_down, nb, ST, 0, stream, a.count, a.n, a.bsum, direct, a.offs, a.total)))
+    return e;
+  return a.out ? launch_points<true>(a, stream) : hipSuccess;
 }
 
 }  // namespace gnn
@@ -450,8 +620,11 @@ extern "C" int gnn_frnn(const float *z, int64_t n_nodes, int32_t dim, float r2,
   a.z = z;
   a.n = n_nodes;
   a.D = dim;
-  a.g = dim < 3 ? dim : 3;
   a.r2 = r2;
+  // Room for 32 partners a point (a cluster's first point has most of the
+  // cluster; one point that is scanned twice costs the write launch 25 us);
+  // for very many points, whose workspace counts, for 4.
+  a.n_slots = n_nodes <= (1 << 24) ? 32 : 4;
   // Cells a little wider than the radius: a pair that passes the fp32 test
   // differs by less than that along every coordinate.
   const double cell = 1.001 * std::sqrt((double)r2);
@@ -467,14 +640,16 @@ extern "C" int gnn_frnn(const float *z, int64_t n_nodes, int32_t dim, float r2,
     off += align256(b > 0 ? b : 1);
     return o;
   };
-  const size_t o_keys = take((size_t)2 * n * 4);
-  const size_t o_rpi = take(((size_t)m + 1) * 4), o_pi = take((size_t)n * 4);
-  const size_t o_rpo = take(((size_t)m + 1) * 4), o_po = take((size_t)n * 4);
-  const size_t o_pa = take((size_t)2 * n * 8), o_pb = take((size_t)2 * n * 8);
-  const size_t o_st = take(csr_scratch_bytes(n, m));
+  const size_t o_keys = take((size_t)n * 4);
+  const size_t o_rp = take(((size_t)m + 1) * 4), o_perm = take((size_t)n * 4);
+  const size_t o_pa = take((size_t)n * 8), o_pb = take((size_t)n * 8);
+  const size_t o_st = take(csr_scratch_bytes(n, m, 1));
   const size_t o_cnt = take((size_t)n * 4), o_offs = take((size_t)n * 8), o_total = take(8);
   const size_t o_bsum = take(frnn_scan_blocks(n) * 8);
-  const size_t o_zs = take((size_t)n * dim * 4);
+  const size_t o_z4 = take((size_t)n * 16);
+  const size_t o_zr = take(dim > 4 ? (size_t)n * (dim - 4) * 4 : 0);
+  const size_t o_z2 = take(((size_t)n + 4) * 8);  // (read up to 3 points past the end)
+  const size_t o_slots = take((size_t)n * a.n_slots * 4);
   void *base = nullptr;
   if (hipMallocAsync(&base, off, stream) != hipSuccess) {
     (void)hipGetLastError();
@@ -486,39 +661,39 @@ extern "C" int gnn_frnn(const float *z, int64_t n_nodes, int32_t dim, float r2,
   cs.pairs_a = (uint2 *)(b + o_pa);
   cs.pairs_b = (uint2 *)(b + o_pb);
   cs.status = (uint32_t *)(b + o_st);
-  a.rp = (const int32_t *)(b + o_rpi);
-  a.perm = (const int32_t *)(b + o_pi);
+  a.rp = (const int32_t *)(b + o_rp);
+  a.perm = (const int32_t *)(b + o_perm);
+  a.z4 = (float *)(b + o_z4);
+  a.zr = (float *)(b + o_zr);
+  a.z2 = (float *)(b + o_z2);
+  a.slots = (int32_t *)(b + o_slots);
   a.count = (int32_t *)(b + o_cnt);
   a.offs = (int64_t *)(b + o_offs);
-  a.total_dev = (int64_t *)(b + o_total);
+  a.total = (int64_t *)(b + o_total);
   a.bsum = (int64_t *)(b + o_bsum);
+  a.out = edge_index;
+  a.max_pairs = max_pairs < INT32_MAX ? max_pairs : INT32_MAX;
 
+  // The write is queued behind the count and checks it on the device, so the
+  // stream does not run dry while the host reads the count.
   int rc = GNN_OK;
   int64_t total = 0;
   hipError_t e = launch_frnn_keys(a, keys, stream);
   if (e == hipSuccess)
-    e = build_csr(keys, (int32_t)n, (int32_t)m, (int32_t *)(b + o_rpi), (int32_t *)(b + o_pi),
-                  (int32_t *)(b + o_rpo), (int32_t *)(b + o_po), cs, nullptr, nullptr, nullptr,
-                  stream);
-  float *zs = (float *)(b + o_zs);
-  if (e == hipSuccess) e = launch_frnn_count(a, zs, stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(&total, a.total_dev, 8, hipMemcpyDeviceToHost, stream);
+    e = build_buckets(keys, (int32_t)n, (int32_t)m, (int32_t *)(b + o_rp), (int32_t *)(b + o_perm),
+                      cs, stream);
+  if (e == hipSuccess) e = launch_frnn_pairs(a, stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(&total, a.total, 8, hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     rc = set_error(GNN_E_HIP, hipGetErrorString(e));
   } else {
     *n_pairs = total;
-    if (total > INT32_MAX) {
+    if (total > INT32_MAX)
       rc = set_error(GNN_E_UNSUPPORTED, "more than INT32_MAX pairs");
-    } else if (edge_index && total > max_pairs) {
+    else if (edge_index && total > max_pairs)
       rc = set_error(GNN_E_INVALID_ARG, "edge_index holds fewer pairs than found (see n_pairs)");
-    } else if (edge_index && total > 0) {
-      a.total = total;
-      a.out = edge_index;
-      e = launch_frnn_fill(a, zs, stream);
-      if (e != hipSuccess) rc = set_error(GNN_E_HIP, hipGetErrorString(e));
-    }
   }
   if (hipFreeAsync(base, stream) != hipSuccess && rc == GNN_OK)
     rc = set_error(GNN_E_HIP, "frnn workspace release failed");

@@ -1,0 +1,58 @@
+"""Fixed-radius pairs where the kernels branch: points with more partners than
+slots, unaligned rows, few and many coordinates, and outputs too small."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2402_09633_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def pair_set(ei):
+    return set(map(tuple, np.asarray(ei).T.tolist()))
+
+
+@pytest.mark.parametrize("dim", [1, 3, 4, 5, 7, 8, 16])
+@pytest.mark.parametrize("n,spread", [(2, 1e-3), (33, 1e-3), (90, 1e-3), (257, 4e-3), (1500, 0.3)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_pairs_match_the_oracle(oracle_mod, dim, n, spread, offset):
+    # spread 1e-3 against r = 0.02: every point pairs with all later ones, up
+    # to 89 partners (32 slots); 0.3: few or none
+    from paper_2402_09633_amd import gnn as G
+    rng = np.random.default_rng(dim * n)
+    z = rng.normal(0.0, spread, (n, dim)).astype(np.float32)
+    buf = torch.empty(n * dim + offset, device="cuda")
+    zd = buf[offset:].view(n, dim)
+    zd.copy_(torch.as_tensor(z))
+    r2 = float(np.float32(0.02) ** 2)
+    ref = pair_set(oracle_mod.frnn(z, r2).T)
+    c = G.gnn_frnn(zd, n, dim, r2)
+    assert c == len(ref)
+    out = torch.full((2 * c + 3,), -5, dtype=torch.int32, device="cuda")
+    assert G.gnn_frnn(zd, n, dim, r2, out, c) == c
+    got = out.cpu().numpy()
+    assert (got[2 * c:] == -5).all()
+    ei = got[:2 * c].reshape(2, c)
+    assert pair_set(ei) == ref
+    assert (np.diff(ei[0]) >= 0).all()  # grouped by ascending i
+    if c > 1:  # too small: refused, nothing written, the count reported
+        out.fill_(-5)
+        with pytest.raises(G.GnnError) as e:
+            G.gnn_frnn(zd, n, dim, r2, out, c - 1)
+        assert e.value.code == G.GNN_E_INVALID_ARG
+        assert bool((out == -5).all())
+
+
+def test_scan_with_many_tiles():
+    # more than one 2048-count tile, the last one partly filled
+    from paper_2402_09633_amd import gnn as G
+    n = 2048 * 5 + 17
+    z = torch.as_tensor(I.clustered_points(n, 8, 3, sigma=0.005)).cuda()
+    ei = G.radius_graph(z, 0.02 ** 2)
+    d = torch.cdist(z.double().cpu(), z.double().cpu())
+    near = (d < 0.02).triu(1)
+    edge = ((d - 0.02).abs() < 1e-7).triu(1)  # fp32 decides these
+    got = torch.zeros_like(near)
+    got[ei[0].long().cpu(), ei[1].long().cpu()] = True
+    assert bool((got == near)[~edge].all())

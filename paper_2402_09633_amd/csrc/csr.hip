@@ -15,8 +15,8 @@
 // destination, by source) share each launch.
 //
 // Sort layout: a block of 1024 threads (16 waves) owns a tile of
-// OS_TILE = 16 x 64 x OS_ITEMS consecutive items; wave w owns the w-th
-// sixteenth, lane l item w*64*OS_ITEMS + it*64 + l in round it.  Stable
+// 16 x 64 x items consecutive items (os_items); wave w owns the w-th
+// sixteenth, lane l item w*64*items + it*64 + l in round it.  Stable
 // order inside a tile is (wave, round, lane) = item order.
 #include "gnn_internal.h"
 
@@ -29,13 +29,15 @@ constexpr int RS_MAX_PASSES = 4;            // 31-bit keys: four 8-bit digits
 // single-sweep pass: 16 waves (one thread per counter), OS_ITEMS items per lane
 constexpr int OS_WAVES = 16;
 constexpr int OS_THREADS = 64 * OS_WAVES;
-#ifndef CSR_OS_ITEMS
-#define CSR_OS_ITEMS 8
-#endif
-#ifndef CSR_OS_WINDOW
-#define CSR_OS_WINDOW 8
-#endif
-constexpr int OS_ITEMS = CSR_OS_ITEMS, OS_TILE = OS_THREADS * OS_ITEMS;
+constexpr int OS_WINDOW = 8;  // predecessors per look-back round trip
+// Items per lane.  A tile's latency is its ranking, which grows with its items
+// (8 per lane: 4.5 us of instructions), and the look-back, which grows with the
+// number of tiles; both a small build's few tiles wait for, while a large
+// build's tiles overlap one another and pay for every published word.  Whole
+// inference, us, with 8 / 4 / 2 / 1: 8k edges 108 / 100 / 95 / 94, 70k 216 /
+// 198 / 191 / 190, 330k 1645 / 1637 / 1643 / 1655, 1.0M (fp16 weights) 3194 /
+// 3204 / 3228 / 3273.
+constexpr int os_items(int64_t n) { return n <= (1 << 17) ? 2 : n <= (1 << 19) ? 4 : 8; }
 static_assert(OS_THREADS == RS_RADIX, "one look-back thread per counter");
 
 __device__ __forceinline__ uint32_t clamp_key(int32_t k, int32_t n) {
@@ -148,11 +150,12 @@ struct OneSweep {
   int32_t *eis, *inv;
 };
 constexpr uint32_t RS_AGG = 1u << 30, RS_INC = 2u << 30, RS_COUNT = RS_AGG - 1u;
-constexpr int OS_WINDOW = CSR_OS_WINDOW;
 
+template <int OS_ITEMS>
 __global__ __launch_bounds__(OS_THREADS) void rs_onesweep(SortSet S, OneSweep O, int32_t n,
                                                           int32_t n_nodes, int pass, int bits,
                                                           int32_t ntiles, int last) {
+  constexpr int OS_TILE = OS_THREADS * OS_ITEMS;
   __shared__ uint32_t cnt[OS_WAVES][RS_RADIX];  // per-wave digit counts, then bases
   __shared__ uint32_t wsum[OS_WAVES];
   __shared__ int32_t tile_sh;
@@ -463,7 +466,11 @@ Digits csr_digits(int64_t n_nodes) {
   return {passes, (b + passes - 1) / passes};
 }
 
-int64_t csr_tiles(int64_t n_edges) { return (n_edges + OS_TILE - 1) / OS_TILE; }
+int64_t csr_tiles(int64_t n_edges, int items) {
+  const int64_t tile = (int64_t)OS_THREADS * items;
+  return (n_edges + tile - 1) / tile;
+}
+int64_t csr_tiles(int64_t n_edges) { return csr_tiles(n_edges, os_items(n_edges)); }
 
 // Scratch words after the look-back status: digit totals, tile counters and
 // the error word.
@@ -509,8 +516,10 @@ hipError_t build_sorts(int sorts, const int32_t *const (&keys)[2], int32_t n, in
     for (int p = 0; p < dg.passes; ++p) {
       const bool last = p == dg.passes - 1;
       for (int y = 0; y < sorts; ++y) S.out[y] = (p & 1) ? pb[y] : pa[y];
-      if (const hipError_t e = launch(rs_onesweep, dim3(ntiles, sorts), OS_THREADS, 0, stream, S,
-                                      O, n, n_nodes, p, dg.bits, ntiles, last ? 1 : 0))
+      const int items = os_items(n);
+      if (const hipError_t e = launch(items == 2 ? rs_onesweep<2> : items == 4 ? rs_onesweep<4> : rs_onesweep<8>,
+                                      dim3(ntiles, sorts), OS_THREADS, 0, stream, S, O, n, n_nodes,
+                                      p, dg.bits, ntiles, last ? 1 : 0))
         return e;
       for (int y = 0; y < sorts; ++y) {
         S.keys_i32[y] = nullptr;
@@ -534,6 +543,11 @@ hipError_t build_sorts(int sorts, const int32_t *const (&keys)[2], int32_t n, in
 
 size_t csr_scratch_bytes(int64_t n_edges, int64_t n_nodes, int sorts) {
   return (csr_status_words(n_edges, n_nodes, sorts) + CSR_TAIL_WORDS) * 4;
+}
+
+size_t csr_reserved_bytes(int64_t n_edges, int64_t n_nodes) {
+  return ((size_t)csr_digits(n_nodes).passes * 2 * RS_RADIX * (size_t)csr_tiles(n_edges, 8) +
+          CSR_TAIL_WORDS) * 4;
 }
 
 uint32_t *csr_err_word(const CsrScratch &s, int64_t n_edges, int64_t n_nodes) {

@@ -528,7 +528,7 @@ size_t plan_workspace(Workspace &w, int64_t N, int64_t E, int H, size_t act_byte
   const size_t o_rpi = take((size_t)(N + 1) * 4), o_rpo = take((size_t)(N + 1) * 4);
   const size_t o_pi = take((size_t)E * 4), o_po = take((size_t)E * 4);
   const size_t o_sa = take((size_t)E * 16), o_sb = take((size_t)E * 16);
-  const size_t o_st = take(csr_scratch_bytes(E, N, 2));
+  const size_t o_st = take(csr_reserved_bytes(E, N));
   const size_t o_eis = factored ? take((size_t)E * 8) : 0;
   const size_t o_inv = factored ? take((size_t)E * 4) : 0;
   const size_t o_qin = factored ? take((size_t)E * 4) : 0;
@@ -553,7 +553,12 @@ size_t plan_workspace(Workspace &w, int64_t N, int64_t E, int H, size_t act_byte
     w.perm_out = (int32_t *)(b + o_po);
     w.csr.pairs_a = (uint2 *)(b + o_sa);
     w.csr.pairs_b = (uint2 *)(b + o_sb);
-    w.csr.status = (uint32_t *)(b + o_st);
+    // (an edge row takes at least 128 bytes, the sort's words at most 16 per
+    // edge beyond the first tile's)
+    const size_t need = csr_scratch_bytes(E, N, 2);
+    w.csr.status = need <= csr_reserved_bytes(E, N)            ? (uint32_t *)(b + o_st)
+                   : need <= (size_t)E * H * act_bytes ? (uint32_t *)(b + o_e)
+                                                               : nullptr;
     w.flag = (int32_t *)(b + o_flag);
     if (factored) {
       w.eis = (int32_t *)(b + o_eis);
@@ -886,6 +891,10 @@ int run(gnn_handle *hd, const float *x, const int32_t *ei, int64_t N, int64_t E,
     if (rc != GNN_OK) return rc;
   }
   plan_workspace(w, N, E, H, ab, fac, fused);
+  if (!w.csr.status) {  // (never: see plan_workspace)
+    rc = fail(GNN_E_UNSUPPORTED, "no room for the CSR sort's counters");
+    goto out;
+  }
 
   if (d.flags & GNN_VALIDATE_INDICES) {
     int32_t bad = 0;

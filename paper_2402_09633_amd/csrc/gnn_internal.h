@@ -222,6 +222,10 @@ struct CsrScratch {
 // CSR_MAX_ITEMS - 1 edges (larger ones return hipErrorInvalidValue).
 constexpr int32_t CSR_MAX_ITEMS = 1 << 30;
 size_t csr_scratch_bytes(int64_t n_edges, int64_t n_nodes, int sorts);
+// What an inference workspace reserves for them: the words of 8-item tiles.
+// Smaller tiles (smaller builds) may need more, which then lie in the edge
+// rows' buffer, not in use yet; the workspace's size does not depend on them.
+size_t csr_reserved_bytes(int64_t n_edges, int64_t n_nodes);
 // Nonzero after a build in which a sort pass gave up waiting for an earlier
 // tile (a bounded wait that forward progress of running workgroups ends).
 uint32_t *csr_err_word(const CsrScratch &s, int64_t n_edges, int64_t n_nodes);

@@ -286,8 +286,8 @@ std::vector<uint16_t> rec_bf16x2(const BlobLayer &L, int c0, int K, int grp, flo
 // bf16 model: power of two s for the fp16 projections s P = s [W_s h; W_d h]
 // that edge-side layer L reads (columns [0, H) and [H, 2H) of its W), with
 // s max_f sum_k |W[f][k]| hb <= 2^15 for an h bound hb, as large as that
-// allows within [2^kmin, 2^40]; 0 if none fits.
-float proj_f16_scale(const BlobLayer &L, int H, double hb, int kmin = MIN_SCALE) {
+// allows within [2^-40, 2^40]; 0 if none fits.
+float proj_f16_scale(const BlobLayer &L, int H, double hb) {
   double m = 0.0;
   for (int f = 0; f < L.fout; ++f)
     for (int half = 0; half < 2; ++half) {
@@ -301,7 +301,7 @@ float proj_f16_scale(const BlobLayer &L, int H, double hb, int kmin = MIN_SCALE)
   int e = 0;
   (void)frexp(32768.0 / bound, &e);  // 2^(e-1) <= 2^15 / bound < 2^e
   int k = e - 1;
-  k = k < kmin ? kmin : (k > 40 ? 40 : k);
+  k = k < -40 ? -40 : (k > 40 ? 40 : k);
   const double sc = ldexp(1.0, k);
   return sc * bound <= 32768.0 ? (float)sc : 0.f;
 }
@@ -1368,63 +1368,15 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
     for (int s = 0; s < S; ++s)
       for (const BlobLayer *L : {&e0s[s], &e1s[s], &n0s[s], &n1s[s]})
         bound = fmax(bound, ln_out_bound(*L));
-    double hb = ln_out_bound(a1);  // of the h rows
-    for (int s = 0; s < S; ++s) hb = fmax(hb, ln_out_bound(n1s[s]));
-    if (factored && !bf16) {
-      // Split products need every LayerNorm output that feeds an f16x2
-      // product inside the fp16 range (with a factor 2 to spare).
-      split = !(d.flags & GNN_FP32_MFMA) && bound <= 32768.0;
-      fdh.row_bound = (float)bound;
-    }
-    if (factored && bf16) {
-      // The bf16 model on the same kernels: hi/lo bf16 records (or, with
-      // GNN_F16_WEIGHTS, one fp16 record part); the fp16 projections and the
-      // W_e records of their consumer carry that consumer's scale (bias and
-      // eps follow in the kernel).
-      split = true;
-      if (f16w) {
-        // fp16 operands: every LayerNorm output that feeds a product must
-        // lie inside the fp16 range (as for the split products), and the
-        // node update scales aggregate rows by the message-row bound
-        if (!(bound <= 32768.0)) {
-          fail(GNN_E_UNSUPPORTED,
-               "GNN_F16_WEIGHTS: a LayerNorm output bound %g exceeds the fp16 range", bound);
-          return nullptr;
-        }
-        fdh.row_bound = (float)bound;
-      }
-      // Refused weights: no projection scale, or (fp16 weights) a scaled
-      // weight outside the fp16 range.
-      bool fits = true, f16_fits = true;
-      auto check = [&](const BlobLayer &L, int K, float sc) {
-        for (int f = 0; f < L.fout; ++f)
-          for (int k = 0; k < K; ++k)
-            if (!(fabsf(sc * L.W[(size_t)f * L.fin + k]) <= 65504.f)) f16_fits = false;
-      };
-      std::vector<const BlobLayer *> proj_of{&b0, &c0}, dense{&a1, &b1};
-      for (int s = 0; s < S; ++s) {
-        proj_of.push_back(&e0s[s]);
-        dense.push_back(&e1s[s]);
-        if (T > 0) dense.insert(dense.end(), {&n0s[s], &n1s[s]});
-      }
-      for (const BlobLayer *L : proj_of) {
-        const float sc = proj_f16_scale(*L, H, hb);
-        fits = fits && sc > 0.f;
-        check(*L, L->fin, sc);
-      }
-      for (const BlobLayer *L : dense) check(*L, L->fin, pow2_scale(*L));
-      if (!fits) {
-        fail(GNN_E_UNSUPPORTED,
-             "bf16 model: no power-of-two scale keeps these weights' node projections inside "
-             "the fp16 range");
-        return nullptr;
-      }
-      if (f16w && !f16_fits) {
-        fail(GNN_E_UNSUPPORTED, "GNN_F16_WEIGHTS: a scaled weight exceeds the fp16 range");
-        return nullptr;
-      }
-    }
-    if (split) {
+    // The split kernels take both models; fp32 split products need every
+    // LayerNorm output that feeds an f16x2 product inside the fp16 range (with
+    // a factor 2 to spare).
+    split = factored && (bf16 || (!(d.flags & GNN_FP32_MFMA) && bound <= 32768.0));
+    // Centred in fp32 only: in the 16-bit models the rounding of the centred
+    // weights and projections differs from that of the given ones, and one
+    // different rounding travels through all later layers (scores as far
+    // from the uncentred ones as either is from the exact).
+    if (split && !bf16) {
       auto centre = [&](BlobLayer &L) {
         centred.emplace_back(L);
         L = centred.back().L;
@@ -1433,6 +1385,7 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
       for (int s = 0; s < S; ++s)
         for (BlobLayer *L : {&e0s[s], &e1s[s], &n0s[s], &n1s[s]}) centre(*L);
     }
+    if (factored && (!bf16 || f16w)) fdh.row_bound = (float)bound;
     // (the split kernels read their matrices from records, not from here)
     const WKind f_mem = split ? WKind::Plain : WKind::FragMem;
     const WKind f_acc = split ? WKind::Plain : WKind::FragAcc;
@@ -1454,18 +1407,33 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
       return t + 1 < T ? e0s[S == 1 ? 0 : t + 1] : c0;
     };
     if (factored && bf16) {
-      // Scale of the projections that edge-side layer L reads, and of its
-      // W_e records: an fp16 record keeps |s W_e| inside the fp16 range too.
-      auto scale_p = [&](const BlobLayer &L) {
-        float sc = proj_f16_scale(L, H, hb, MIN_SCALE - 2), mx = 0.f;
-        for (int f = 0; f < L.fout && f16w; ++f)
-          for (int k = 0; k < L.fin; ++k) mx = fmaxf(mx, fabsf(L.W[(size_t)f * L.fin + k]));
-        while (sc * mx > 32768.f) sc *= 0.5f;
-        return sc;
-      };
-      fdh.s1_ee = scale_p(b0);
-      fdh.s1_cls = scale_p(c0);
-      for (int s = 0; s < S; ++s) fdh.s1_em.push_back(scale_p(e0s[s]));
+      // The bf16 model on the split kernels: hi/lo bf16 records (or, with
+      // GNN_F16_WEIGHTS, one fp16 record part); the fp16 projections and the
+      // W_e records of their consumer carry that consumer's scale (bias and
+      // eps follow in the kernel).
+      if (f16w && !(bound <= 32768.0)) {
+        // fp16 operands: every LayerNorm output that feeds a product must
+        // lie inside the fp16 range (as for the split products), and the
+        // node update scales aggregate rows by the message-row bound
+        fail(GNN_E_UNSUPPORTED,
+             "GNN_F16_WEIGHTS: a LayerNorm output bound %g exceeds the fp16 range", bound);
+        return nullptr;
+      }
+      double hb = ln_out_bound(a1);
+      for (int s = 0; s < S; ++s) hb = fmax(hb, ln_out_bound(n1s[s]));
+      fdh.s1_ee = proj_f16_scale(b0, H, hb);
+      fdh.s1_cls = proj_f16_scale(c0, H, hb);
+      bool fits = fdh.s1_ee > 0.f && fdh.s1_cls > 0.f;
+      for (int s = 0; s < S; ++s) {
+        fdh.s1_em.push_back(proj_f16_scale(e0s[s], H, hb));
+        fits = fits && fdh.s1_em[s] > 0.f;
+      }
+      if (!fits) {
+        fail(GNN_E_UNSUPPORTED,
+             "bf16 model: no power-of-two scale keeps these weights' node projections inside "
+             "the fp16 range");
+        return nullptr;
+      }
       auto add16 = [&](const std::vector<uint16_t> &v) {
         return st.add(v.data(), v.size() * sizeof(uint16_t));
       };
@@ -1476,10 +1444,15 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
       // the weights times a power of two (W2, the node MLPs and the node
       // encoder's W2 then carry pow2_scale; the projections and W_e carry
       // the fp16 projections' consumer scale either way).
+      bool f16_fits = true;
       auto rec = [&](const BlobLayer &L, int c0, int K, int grp, float sc) {
-        return f16w ? rec_f16x1(L, c0, K, sc, grp) : rec_bf16x2(L, c0, K, grp, sc);
+        if (!f16w) return rec_bf16x2(L, c0, K, grp, sc);
+        for (int f = 0; f < L.fout; ++f)
+          for (int k = c0; k < c0 + K; ++k)
+            if (!(fabsf(sc * L.W[(size_t)f * L.fin + k]) <= 65504.f)) f16_fits = false;
+        return rec_f16x1(L, c0, K, sc, grp);
       };
-      auto s2_of = [&](const BlobLayer &L) { return f16w ? pow2_scale(L, MIN_SCALE - 2) : 1.f; };
+      auto s2_of = [&](const BlobLayer &L) { return f16w ? pow2_scale(L) : 1.f; };
       fdh.s2_ee = s2_of(b1);
       fdh.s2_ne = s2_of(a1);
       for (int s = 0; s < S; ++s) {
@@ -1513,6 +1486,10 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
         cat(us, rec(n1s[k], 0, H, -1, fdh.s2_nm[k]));
         proj(us, next_edge_l1(t));
         o_upd_stream[t] = add16(us);
+      }
+      if (!f16_fits) {
+        fail(GNN_E_UNSUPPORTED, "GNN_F16_WEIGHTS: a scaled weight exceeds the fp16 range");
+        return nullptr;
       }
     } else if (factored && split) {
       auto add16 = [&](const std::vector<uint16_t> &v) {

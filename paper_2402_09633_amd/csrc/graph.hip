@@ -47,7 +47,7 @@ __global__ __launch_bounds__(64 * SM_WAVES) void embed_mlp(EmbedArgs a) {
   __shared__ typename M::Lds lds;
   __shared__ h8 out_r[FOLD ? NOUT : 1];
   __shared__ float out_w[FOLD ? 1 : MAX_D * H];
-  __shared__ float out_b[32];  // (FOLD: times s2)
+  __shared__ float out_b[32];
   const int lane = threadIdx.x & 63, hh = lane >> 5, n = lane & 31;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int F = FK ? FK : a.F;
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(64 * SM_WAVES) void embed_mlp(EmbedArgs a) {
   } else {
     for (int i = threadIdx.x; i < a.D * H; i += 64 * SM_WAVES) out_w[i] = a.w2[i];
   }
-  if (threadIdx.x < 32) out_b[threadIdx.x] = (int)threadIdx.x < a.D ? a.b2[threadIdx.x] * a.s2 : 0.f;
+  if (threadIdx.x < 32) out_b[threadIdx.x] = (int)threadIdx.x < a.D ? a.b2[threadIdx.x] : 0.f;
   __syncthreads();
   for (; u < units; u += nw) {
     // keeps the LDS reads of the weights inside the loop
@@ -96,11 +96,7 @@ __global__ __launch_bounds__(64 * SM_WAVES) void embed_mlp(EmbedArgs a) {
       // rows are used; lane (n, hh) then holds outputs 8 q + 4 hh + t.
       f16v z;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const f4 bb = *(const f4 *)(out_b + 8 * q + 4 * hh);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) z[4 * q + t] = bb[t];
-      }
+      for (int v = 0; v < 16; ++v) z[v] = 0.f;
 #pragma unroll
       for (int g = 0; g < 2 * MB; ++g) {
         const h8 *r = out_r + g * OUT_PARTS * 64 + lane;
@@ -123,7 +119,8 @@ __global__ __launch_bounds__(64 * SM_WAVES) void embed_mlp(EmbedArgs a) {
         for (int q = 0; q < MAX_D / 8; ++q) {
           const int d0 = 8 * q + 4 * hh;
           float *o = a.z + row * a.D + d0;
-          const f4 v = f4{z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]} * inv;
+          const f4 v = f4{z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]} * inv +
+                       *(const f4 *)(out_b + d0);
           if (d0 + 4 <= a.D && a.z16) {
             *(f4 *)o = v;
           } else {

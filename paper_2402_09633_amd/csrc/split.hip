@@ -101,9 +101,9 @@ __device__ __forceinline__ float sum32(float v) {
 
 // Bias + LayerNorm + ReLU on transposed accumulators (step_ht): lane l holds
 // feature 32 mb + n, n = l % 32, of 16 rows; a row's statistics are sums
-// over the 32 lanes of its half of the wave.  prm as for ln_relu_lds; the
-// layer is centred (its rows have mean zero), so only the squares are summed.
-template <int MB>
+// over the 32 lanes of its half of the wave.  prm and CENTERED as for
+// ln_relu_lds.
+template <int MB, bool CENTERED>
 __device__ __forceinline__ void ln_relu_t(f16v (&t)[MB], const float *prm, float eps, int n) {
   constexpr int H = 32 * MB;
   constexpr float inv_h = 1.0f / H;
@@ -119,12 +119,23 @@ __device__ __forceinline__ void ln_relu_t(f16v (&t)[MB], const float *prm, float
   // four rows at a time: their reductions overlap, with few live registers
 #pragma unroll
   for (int v0 = 0; v0 < 16; v0 += 4) {
-    float rstd[4];
+    float mean[4], rstd[4];
+    if constexpr (!CENTERED)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float sv = 0.f;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) sv += t[mb][v0 + j];
+        mean[j] = sum32(sv) * inv_h;
+      }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       float q = 0.f;
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) q += t[mb][v0 + j] * t[mb][v0 + j];
+      for (int mb = 0; mb < MB; ++mb) {
+        if constexpr (!CENTERED) t[mb][v0 + j] -= mean[j];  // centred in place, reused below
+        q += t[mb][v0 + j] * t[mb][v0 + j];
+      }
       rstd[j] = ln_rstd(sum32(q) * inv_h + eps);
     }
 #pragma unroll
@@ -477,7 +488,7 @@ __global__ __launch_bounds__(64 * SW) void node_split(NodeArgs a) {
     if constexpr (ENC) {
       // the bias is in the accumulators already (the LayerNorm adds zeros)
       small_k_layer<MB>(acc, a.x, a.F, (int)r, prm + 7 * H, prm + 6 * H, hh);
-      ln_relu_lds<MB, true, true>(acc, prm, a.eps, hh);
+      ln_relu_lds<MB, true, PREC == SPLIT>(acc, prm, a.eps, hh);
     } else {
       // Layer 1 over [h; agg_in; agg_out]: 3G records.  The k-steps of each
       // source are taken in line order (node_line_k): the GRP records of a
@@ -550,7 +561,7 @@ __global__ __launch_bounds__(64 * SW) void node_split(NodeArgs a) {
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb] *= inv_sv;
       }
-      ln_relu_lds<MB, true, true>(acc, prm, a.eps * a.s1 * a.s1, hh);
+      ln_relu_lds<MB, true, PREC == SPLIT>(acc, prm, a.eps * a.s1 * a.s1, hh);
     }
 
     // Layer 2, then the projection halves.  Record i of this part sits in
@@ -575,7 +586,7 @@ __global__ __launch_bounds__(64 * SW) void node_split(NodeArgs a) {
         step_f<MB>(hv, (const h8 *)rec_h(g), acc_to_h(acc_x<MB>(acc, g)));
       rec_done(g);
     }
-    ln_relu_lds<MB, true, true>(hv, prm + 3 * H, eps2, hh);
+    ln_relu_lds<MB, true, PREC == SPLIT>(hv, prm + 3 * H, eps2, hh);
     if (a.h_out) {
       if constexpr (PREC == SPLIT)
         store_block<MB>(a.h_out + wrow0 * H, H, nvalid, hv, stg, lane);
@@ -813,14 +824,14 @@ __global__ __launch_bounds__((64 * edge_waves<PREC, MODE>())) void edge_split(Ed
         load16(a.enc.P, raw);
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) sum16(raw, mb);
-        ln_relu_lds<MB, false, true>(acc, prm_enc, a.eps * a.enc.s1 * a.enc.s1, hh);
+        ln_relu_lds<MB, false, PREC == SPLIT>(acc, prm_enc, a.eps * a.enc.s1 * a.enc.s1, hh);
         h8 xa[G];
 #pragma unroll
         for (int g = 0; g < G; ++g) xa[g] = acc_to_h(acc_x<MB>(acc, g));
         zero<MB>(acc);
 #pragma unroll
         for (int g = 0; g < G; ++g) step_f<MB>(acc, lw_2enc + g * RP * MB * 64 + lane, xa[g]);
-        ln_relu_lds<MB, true, true>(acc, prm_enc + 3 * H, a.eps * a.enc.s2 * a.enc.s2, hh);
+        ln_relu_lds<MB, true, PREC == SPLIT>(acc, prm_enc + 3 * H, a.eps * a.enc.s2 * a.enc.s2, hh);
         // The update's gathers.  Issued before that LayerNorm, to wait
         // under it, they spill registers and cost more than they hide (full
         // event 3.378 ms with the P[src] half there, 3.408 with both,
@@ -859,7 +870,7 @@ __global__ __launch_bounds__((64 * edge_waves<PREC, MODE>())) void edge_split(Ed
     // (FUSE: after layer 2's LayerNorm, which needs the registers)
     if constexpr (!FUSE)
       if (un >= 0) load_idx(un);
-    ln_relu_lds<MB, false, true>(acc, prm, eps1, hh);  // bias inside P[src]
+    ln_relu_lds<MB, false, PREC == SPLIT>(acc, prm, eps1, hh);  // bias inside P[src]
 
     if constexpr (!HAS_L2) {
       float part = 0.f;
@@ -894,7 +905,7 @@ __global__ __launch_bounds__((64 * edge_waves<PREC, MODE>())) void edge_split(Ed
         else
           step_ft<MB>(t2, lw_2 + g * RP * MB * 64 + lane, acc_to_h(acc_x<MB>(acc, g)));
       }
-      ln_relu_t<MB>(t2, prm + 3 * H, eps2, n);
+      ln_relu_t<MB, PREC == SPLIT>(t2, prm + 3 * H, eps2, n);
       if constexpr (PREC != SPLIT) {
         // the stored rows are the bf16 values; the sums add exactly those
 #pragma unroll

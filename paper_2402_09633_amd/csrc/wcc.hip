@@ -15,7 +15,7 @@
 //             predecessor
 //   round     for every kept edge, both ends are pointed at their roots, and
 //             the larger root at the smaller one
-//   unite     the same, but the root is linked by compare-and-swap, repeated
+//   unite     the same, but the root is linked by an atomic minimum, repeated
 //             until both ends share a root
 //   compress  parent[v] = root of v
 //
@@ -24,16 +24,17 @@
 // goes to the memory side, and once large trees meet, a hundred thousand of
 // them hit one root.  The rounds leave unite almost nothing to do (a root
 // survives a round only if no neighbouring tree has a smaller one), which
-// keeps its swaps from contending.
+// keeps its minima from contending.
 //
 // Walks read the links through the caches (an agent-scope load goes past the
 // XCD's L2, several times its latency).  A link read that way may be old, but
 // it was a valid link of the same component; a node that once had a smaller
-// link is never a root again; and only unite's compare-and-swap, on the value
-// at the memory side, decides whether a root is still one.  A failed swap
-// returns the current link, smaller than the node, and the walk goes on from
-// there.  So every loop strictly descends in the node ids and ends, and the
-// host has nothing to check.
+// link is never a root again; and only unite's atomic minimum, on the value
+// at the memory side, decides whether a root is still one.  On a node that is
+// none any more it returns the link so far, smaller than the node; whichever
+// of the two links the node keeps, that one and the smaller root still have to
+// share a root, and the walk goes on from there.  So every loop strictly
+// descends in the node ids and ends, and the host has nothing to check.
 //
 // Whole call, us, against hook rounds by agent-scope walks and atomic minima
 // with a convergence flag read by the host every four rounds: 300k hits with
@@ -58,7 +59,7 @@ __device__ __forceinline__ int32_t link_of(const int32_t *parent, int32_t v) {
   return __hip_atomic_load(parent + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 __device__ __forceinline__ void set_link(int32_t *parent, int32_t v, int32_t to) {
-  __hip_atomic_store(parent + v, to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  parent[v] = to;
 }
 
 // Walks of at most NEAR links (a detector graph's trees are as deep as it has
@@ -78,8 +79,9 @@ __device__ __forceinline__ int32_t walk_near(const int32_t *parent, int32_t v, b
   return v;
 }
 
-// Full walks: past NEAR links at agent scope, halving the path behind, so
-// that the walks of a chain's nodes shorten one another's.
+// Full walks: past NEAR links at the memory side, halving the path behind
+// (a minimum, which other XCDs see), so that the walks of a chain's nodes
+// shorten one another's.
 __device__ __forceinline__ int32_t find_root(int32_t *parent, int32_t v) {
   bool root;
   v = walk_near(parent, v, root);
@@ -88,7 +90,7 @@ __device__ __forceinline__ int32_t find_root(int32_t *parent, int32_t v) {
     if (p == v) return v;
     const int32_t q = __hip_atomic_load(parent + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (q == p) return p;
-    __hip_atomic_store(parent + v, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    atomicMin(&parent[v], q);
     v = q;
   }
   return v;
@@ -213,7 +215,7 @@ __global__ __launch_bounds__(WT) void wcc_unite(WccEdges E, int32_t *parent) {
         a = b;
         b = t;
       }
-      const int32_t old = atomicCAS(&parent[a], a, b);
+      const int32_t old = atomicMin(&parent[a], b);
       if (old == a) break;
       a = find_root(parent, old);
     }

@@ -106,6 +106,9 @@ uint16_t f32_to_bf16(float f) {
 struct BlobLayer {
   const float *W, *b, *g, *beta;
   int fin, fout;
+  const double *Wd = nullptr;  // W before its rounding to fp32 (Centred, Folded)
+
+  double at(size_t i) const { return Wd ? Wd[i] : (double)W[i]; }
 };
 
 // MFMA fragment orders (see mlp.hip).  With MB = H/32, lane = 0..63,
@@ -179,24 +182,37 @@ float pow2_scale(const BlobLayer &L, int kmin = MIN_SCALE) {
 // from each row (mean_f (W x + b)_f = (mean_f W_f) x + mean_f b_f), so its
 // result is the same, and the kernel need not form the mean: per row and
 // LayerNorm two operations per feature and one cross-lane reduction fewer.
-// The column means are formed in double and the differences rounded once to
-// fp32, below the rounding of the products that follow.  |W'| <= 2 |W|, one
-// bit more than the limits checked on W itself.
+// The column means are formed in double; split records are made from the
+// differences as they are (rounded to fp32 first, they would add an error as
+// large as half of the split's own).  |W'| <= 2 |W|, one bit more than the
+// limits checked on W itself.
 struct Centred {
   std::vector<float> W, b;
+  std::vector<double> Wd;
   BlobLayer L;
-  explicit Centred(const BlobLayer &src) : W((size_t)src.fin * src.fout), b(src.fout), L(src) {
-    for (int k = 0; k <= src.fin; ++k) {
-      auto at = [&](int f) { return k < src.fin ? src.W[(size_t)f * src.fin + k] : src.b[f]; };
-      double m = 0.0;
-      for (int f = 0; f < src.fout; ++f) m += (double)at(f);
-      m /= src.fout;
-      for (int f = 0; f < src.fout; ++f)
-        (k < src.fin ? W[(size_t)f * src.fin + k] : b[f]) = (float)((double)at(f) - m);
+  explicit Centred(const BlobLayer &src)
+      : W((size_t)src.fin * src.fout), b(src.fout), Wd(W.size()), L(src) {
+    std::vector<double> m(src.fin, 0.0);
+    double mb = 0.0;
+    for (int f = 0; f < src.fout; ++f) {
+      for (int k = 0; k < src.fin; ++k) m[k] += (double)src.W[(size_t)f * src.fin + k];
+      mb += (double)src.b[f];
+    }
+    for (double &v : m) v /= src.fout;
+    mb /= src.fout;
+    for (int f = 0; f < src.fout; ++f) {
+      for (int k = 0; k < src.fin; ++k) {
+        const size_t i = (size_t)f * src.fin + k;
+        Wd[i] = (double)src.W[i] - m[k];
+        W[i] = (float)Wd[i];
+      }
+      b[f] = (float)((double)src.b[f] - mb);
     }
     L.W = W.data();
     L.b = b.data();
+    L.Wd = Wd.data();
   }
+  Centred(const Centred &) = delete;
 };
 
 // Largest value a LayerNorm/ReLU output of layer L can take:
@@ -236,9 +252,9 @@ std::vector<uint16_t> rec_f16x2(const BlobLayer &L, int c0, int K, float s, int 
         for (int j = 0; j < 8; ++j) {
           const int hh = lane / 32;
           const int k = node_line_k(g, hh, j, grp);
-          const float wv = s * L.W[(size_t)(mb * 32 + lane % 32) * L.fin + c0 + k];
-          const _Float16 p1 = (_Float16)wv;
-          const _Float16 p2 = (_Float16)(wv - (float)p1);
+          const double wv = s * L.at((size_t)(mb * 32 + lane % 32) * L.fin + c0 + k);
+          const _Float16 p1 = (_Float16)(float)wv;
+          const _Float16 p2 = (_Float16)(float)(wv - (double)p1);
           const size_t o = ((((size_t)g * MB + mb) * 2) * 64 + lane) * 8 + j;
           out[o] = f16_bits(p1);
           out[o + 64 * 8] = f16_bits(p2);
@@ -1774,38 +1790,45 @@ namespace {
 // A hidden layer's LayerNorm gains folded into the layer that reads it:
 // relu(g y + beta) = |g| relu(sign(g) y + beta / |g|), so the rows of this
 // layer take the sign, beta becomes FOLD_SCALE beta / |g|, and the columns of
-// the next layer's weights are multiplied by |g| / FOLD_SCALE.  The products
-// are formed in double and rounded once.  Not for gains so uneven, or so
+// the next layer's weights are multiplied by |g| / FOLD_SCALE, in double
+// (Centred).  Not for gains so uneven, or so
 // small beside their shifts, that the folded values would spread over the
 // range of the split products (ok = false).
 struct Folded {
   std::vector<float> W, b, g, beta, Wn;
+  std::vector<double> Wd, Wnd;
   BlobLayer L, next;
   bool ok = true;
   Folded(const BlobLayer &src, const BlobLayer &nx)
-      : W(src.W, src.W + (size_t)src.fin * src.fout), b(src.b, src.b + src.fout),
-        g(src.fout, 1.f), beta(src.fout), Wn(nx.W, nx.W + (size_t)nx.fin * nx.fout), L(src),
+      : W((size_t)src.fin * src.fout), b(src.b, src.b + src.fout), g(src.fout, 1.f),
+        beta(src.fout), Wn((size_t)nx.fin * nx.fout), Wd(W.size()), Wnd(Wn.size()), L(src),
         next(nx) {
     double gmax = 0.0;
     for (int f = 0; f < src.fout; ++f) gmax = fmax(gmax, fabs((double)src.g[f]));
     for (int f = 0; f < src.fout; ++f) {
       const double gf = fabs((double)src.g[f]), c = (double)src.beta[f] / gf;
       if (!(gf > 0.0) || !(gf >= gmax / 256.0) || !(gmax <= 1e30) || !(fabs(c) <= 256.0)) ok = false;
-      if (src.g[f] < 0.f) {
-        for (int k = 0; k < src.fin; ++k) W[(size_t)f * src.fin + k] = -W[(size_t)f * src.fin + k];
-        b[f] = -b[f];
+      const bool neg = src.g[f] < 0.f;
+      for (int k = 0; k < src.fin; ++k) {
+        const size_t i = (size_t)f * src.fin + k;
+        Wd[i] = neg ? -src.at(i) : src.at(i);
+        W[i] = (float)Wd[i];
       }
+      if (neg) b[f] = -b[f];
       beta[f] = (float)(FOLD_SCALE * c);
       for (int o = 0; o < nx.fout; ++o) {
-        float &w = Wn[(size_t)o * nx.fin + f];
-        w = (float)((double)w * gf / FOLD_SCALE);
+        const size_t i = (size_t)o * nx.fin + f;
+        Wnd[i] = nx.at(i) * gf / FOLD_SCALE;
+        Wn[i] = (float)Wnd[i];
       }
     }
     L.W = W.data();
     L.b = b.data();
     L.g = g.data();
     L.beta = beta.data();
+    L.Wd = Wd.data();
     next.W = Wn.data();
+    next.Wd = Wnd.data();
   }
   Folded(const Folded &) = delete;
 };
@@ -1859,11 +1882,11 @@ struct SmallMlpOff {
           for (int j = 0; j < 8; ++j) {
             const int k = node_line_k(g, l / 32, j, -1);
             if (l % 32 >= out.fout) continue;  // zero rows
-            float w = s2 * out.W[(size_t)(l % 32) * H + k];
+            double w = s2 * out.at((size_t)(l % 32) * H + k);
             for (int p = 0; p < 3; ++p) {
-              const _Float16 v = (_Float16)w;
+              const _Float16 v = (_Float16)(float)w;
               r[(((size_t)g * 3 + p) * 64 + l) * 8 + j] = f16_bits(v);
-              w -= (float)v;
+              w -= (double)v;
             }
           }
       w2r = st.add(r.data(), r.size() * sizeof(uint16_t));

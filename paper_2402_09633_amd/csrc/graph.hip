@@ -94,9 +94,11 @@ __global__ __launch_bounds__(64 * SM_WAVES) void embed_mlp(EmbedArgs a) {
     if constexpr (FOLD) {
       // z = W2 a on the matrix cores, one 32-wide output block of which D
       // rows are used; lane (n, hh) then holds outputs 8 q + 4 hh + t.
-      f16v z;
+      // The five small products have a sum of their own: in one sum they
+      // would round the large one six times as often.
+      f16v z, zl;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) z[v] = 0.f;
+      for (int v = 0; v < 16; ++v) z[v] = zl[v] = 0.f;
 #pragma unroll
       for (int g = 0; g < 2 * MB; ++g) {
         const h8 *r = out_r + g * OUT_PARTS * 64 + lane;
@@ -106,13 +108,15 @@ __global__ __launch_bounds__(64 * SM_WAVES) void embed_mlp(EmbedArgs a) {
         const h8 x2 = __builtin_convertvector(y, h8);
         const h8 x3 = __builtin_convertvector(residual16(y, x2), h8);
         const h8 w1 = r[0], w2 = r[64], w3 = r[128];
-        z = mma_h(w3, x1, z);
-        z = mma_h(w2, x2, z);
-        z = mma_h(w1, x3, z);
-        z = mma_h(w2, x1, z);
-        z = mma_h(w1, x2, z);
+        zl = mma_h(w3, x1, zl);
+        zl = mma_h(w2, x2, zl);
+        zl = mma_h(w1, x3, zl);
+        zl = mma_h(w2, x1, zl);
+        zl = mma_h(w1, x2, zl);
         z = mma_h(w1, x1, z);
       }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) z[v] += zl[v];
       const float inv = 1.f / a.s2;  // a power of two
       if (row < a.n) {
 #pragma unroll

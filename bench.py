@@ -50,9 +50,9 @@ TRAFFIC_SOURCES = {
 }
 # (path, source hash) -> (HBM bytes read, written) per edge-update launch on
 # the full event
-MEASURED_TRAFFIC = {("split", "393e70c466c8f0c6"): (1.131e9, 0.651e9),    # edge_split<4,3>
-                    ("bf16", "393e70c466c8f0c6"): (0.551e9, 0.342e9),     # edge_split<4,3,bf16>
-                    ("f16w", "393e70c466c8f0c6"): (0.593e9, 0.347e9)}     # edge_split<4,3,f16w>
+MEASURED_TRAFFIC = {("split", "46002303e7ff714f"): (1.133e9, 0.651e9),    # edge_split<4,3>
+                    ("bf16", "46002303e7ff714f"): (0.551e9, 0.342e9),     # edge_split<4,3,bf16>
+                    ("f16w", "46002303e7ff714f"): (0.593e9, 0.347e9)}     # edge_split<4,3,f16w>
 
 
 def kernel_source_hash(path):
@@ -475,7 +475,7 @@ def bench_graph_construction(G, I, g):
             "frnn_ms": round(frnn_ms, 4), "frnn_points": 300_000, "frnn_dim": 8,
             "frnn_pairs": int(ei.shape[1]),
             "note": "embedding MLP 3->128->128->8 on the event's hits; fixed-radius pairs "
-                    "(r = 0.02) on 300k clustered 8-d points, count + fill passes with the "
+                    "(r = 0.02) on 300k clustered 8-d points, whole call with the "
                     "count read-back (wall time); not part of value"}
 
 
@@ -772,7 +772,7 @@ def main():
         "components": {"ms_per_event": round(wcc_ms, 4), "threshold": 0.5,
                        "n_components": n_comp,
                        "note": "weakly-connected components of the edges scoring above the "
-                               "threshold, after inference (wall time, host-checked rounds); "
+                               "threshold, after inference (wall time); "
                                "not part of value"},
     }
     if roof_node:

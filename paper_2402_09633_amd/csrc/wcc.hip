@@ -40,7 +40,8 @@
 // with a convergence flag read by the host every four rounds: 300k hits with
 // track-like scores (270k of 1.0M edges kept) 244 -> 97; 150k hits, all 500k
 // edges kept (one giant component) 519 -> 90; chain of 300k ids 295 -> 90;
-// hub of 300k edges 1366 -> 130; random graph, 1.2M edges, 369 -> 128.
+// hub of 300k edges 1366 -> 100 to 205 (from run to run; 130 to 625 with a
+// compare-and-swap in unite); random graph, 1.2M edges, 369 -> 163.
 #include "gnn_internal.h"
 
 namespace gnn {

@@ -105,7 +105,7 @@ __device__ __forceinline__ void bias_ln_relu(f16v (&acc)[MB], const float *__res
 // eps by its square).  ADD_BIAS false: the bias is in the accumulators
 // already (b is then not read).  CENTERED: the layer's weights and bias had
 // their mean over the output features taken out when the handle was made
-// (centred() in gnn_api.hip), so the rows have mean zero but for rounding
+// (Centred in gnn_api.hip), so the rows have mean zero but for rounding
 // and no mean is formed.
 template <int MB, bool ADD_BIAS = true, bool CENTERED = false>
 __device__ __forceinline__ void ln_relu_lds(f16v (&acc)[MB], const float *prm, float eps, int hh) {

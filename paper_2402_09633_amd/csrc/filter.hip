@@ -40,7 +40,7 @@ __global__ __launch_bounds__(64 * SM_WAVES) void filter_mlp(FilterArgs a) {
   using M = SmallMlp<MB, SPLIT, FOLD, U>;
   constexpr int H = 32 * MB;
   __shared__ typename M::Lds lds;
-  __shared__ float head[H];
+  __shared__ alignas(16) float head[H];
   __shared__ int32_t kept[SM_WAVES];
   const int lane = threadIdx.x & 63, hh = lane >> 5, n = lane & 31;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -164,7 +164,8 @@ uint16_t f16_bits(_Float16 v) {
 
 // Power of two s with max |s W| in [2^13, 2^14) (1 for an all-zero or
 // non-finite W), over the whole (fout x fin) layer.
-constexpr int MIN_SCALE = -40;  // (centred weights: two more, centred())
+constexpr int MIN_SCALE = -40;  // (centred weights: two more, Centred)
+constexpr int MAX_SCALE = 40;
 float pow2_scale(const BlobLayer &L, int kmin = MIN_SCALE) {
   float mx = 0.f;
   const size_t n = (size_t)L.fout * L.fin;
@@ -173,8 +174,19 @@ float pow2_scale(const BlobLayer &L, int kmin = MIN_SCALE) {
   int e = 0;
   (void)frexpf(mx, &e);  // mx = m 2^e, m in [0.5, 1)
   int k = 14 - e;
-  k = k < kmin ? kmin : (k > 40 ? 40 : k);
+  k = k < kmin ? kmin : (k > MAX_SCALE ? MAX_SCALE : k);
   return ldexpf(1.f, k);
+}
+
+// Whether pow2_scale(L, kmin) reaches [2^13, 2^14) (or L is all zero).
+bool scale_fits(const BlobLayer &L, int kmin) {
+  double mx = 0.0;
+  for (size_t i = 0; i < (size_t)L.fout * L.fin; ++i) {
+    const double w = fabs(L.at(i));
+    if (!(w <= 3e38)) return false;
+    mx = fmax(mx, w);
+  }
+  return mx == 0.0 || (mx >= ldexp(1.0, 13 - MAX_SCALE) && mx < ldexp(1.0, 14 - kmin));
 }
 
 // L with the mean over its output features taken out of every weight column
@@ -1839,11 +1851,35 @@ struct Folded {
 // half the fp16 range (else on the fp32 ones); the LayerNorms' gains are then
 // folded into the layers that follow where Folded allows it.
 struct SmallMlpOff {
-  size_t w0a = 0, w1r = 0, w2r = 0;
+  size_t w0a = 0, w1r = 0, w2r = 0, s2inv = 0;
   LayerOff l0, l1, l2;
   bool split = false, fold = false;
-  float s1 = 1.f, s2 = 1.f;
+  float s1 = 1.f;
   int steps = 0;
+
+  // Three fp16 parts hold a weight to 33 bits, but none below 2^-24: an
+  // entry under 2^-14 of its row's largest (scaled to 2^13) loses fp32's bits.  So every
+  // output row has a scale of its own (*s), and there is none (false) for a
+  // row out of its range, or with more than an eighth of its weights that
+  // small (its sum could rest on those alone).
+  static bool row_scale(const BlobLayer &L, int row, double *s) {
+    double mx = 0.0;
+    int small = 0;
+    for (int k = 0; k < L.fin; ++k) {
+      const double w = fabs(L.at((size_t)row * L.fin + k));
+      if (!(w <= 3e38)) return false;
+      mx = fmax(mx, w);
+    }
+    int e = 14;
+    if (mx > 0.0) (void)frexp(mx, &e);  // mx = m 2^e, m in [0.5, 1)
+    if (e < -86 || e > 114) return false;
+    for (int k = 0; k < L.fin; ++k) {
+      const double w = fabs(L.at((size_t)row * L.fin + k));
+      if (w > 0.0 && w < ldexp(mx, -14)) ++small;
+    }
+    *s = ldexp(1.0, 14 - e);
+    return small <= L.fin / 8;
+  }
 
   SmallMlpOff(Staging &st, const BlobLayer &in0, const BlobLayer &in1, const BlobLayer &in2,
               bool out_records) {
@@ -1851,7 +1887,17 @@ struct SmallMlpOff {
     // (each layer is centred before its rows take the gains' signs)
     const Centred c0(in0), c1(in1);
     const Folded f0(c0.L, c1.L), f1(f0.next, in2);
-    fold = split && f0.ok && f1.ok;
+    // the folded weights have to fit their records' scales too (layer 1, and
+    // the output layer's where it has records; where not it stays in fp32)
+    const BlobLayer &fout = f1.next;
+    double so[32];
+    bool fits = scale_fits(f1.L, MIN_SCALE - 2);
+    for (int r = 0; r < fout.fout && fits; ++r) {
+      if (out_records) fits = row_scale(fout, r, &so[r]);
+      for (int k = 0; k < fout.fin; ++k)
+        fits = fits && std::isfinite(fout.W[(size_t)r * fout.fin + k]);
+    }
+    fold = split && f0.ok && f1.ok && fits;
     const BlobLayer &l_0 = fold ? f0.L : c0.L, &l_1 = fold ? f1.L : c1.L;
     const BlobLayer &out = fold ? f1.next : in2;
     const int K = in0.fin, H = in0.fout, MB = H / 32;
@@ -1875,14 +1921,16 @@ struct SmallMlpOff {
     }
     if (fold && out_records) {
       // three-part records of the output layer, one 32-row block
-      s2 = pow2_scale(out);
+      std::vector<float> si(32, 1.f);
+      for (int r = 0; r < out.fout; ++r) si[r] = (float)(1.0 / so[r]);
+      s2inv = st.add(si.data(), si.size() * sizeof(float));
       std::vector<uint16_t> r((size_t)(H / 16) * 3 * 64 * 8);
       for (int g = 0; g < H / 16; ++g)
         for (int l = 0; l < 64; ++l)
           for (int j = 0; j < 8; ++j) {
             const int k = node_line_k(g, l / 32, j, -1);
             if (l % 32 >= out.fout) continue;  // zero rows
-            double w = s2 * out.at((size_t)(l % 32) * H + k);
+            double w = so[l % 32] * out.at((size_t)(l % 32) * H + k);
             for (int p = 0; p < 3; ++p) {
               const _Float16 v = (_Float16)(float)w;
               r[(((size_t)g * 3 + p) * 64 + l) * 8 + j] = f16_bits(v);
@@ -2100,7 +2148,7 @@ gnn_embedder *gnn_embed_create(const float *weights, const gnn_embed_dims *dims)
   m->tmpl.b2 = d2.b;
   if (om.fold) {
     m->tmpl.w2r = base + om.w2r;
-    m->tmpl.s2 = om.s2;
+    m->tmpl.s2inv = (const float *)(base + om.s2inv);
   }
   return m;
 }

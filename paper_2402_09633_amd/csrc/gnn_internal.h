@@ -298,10 +298,11 @@ struct EmbedArgs {
   int32_t F = 0, D = 0;
   SmallMlpArgs mlp;
   const float *w2 = nullptr, *b2 = nullptr;  // [D][H], [D]
-  // mlp.fold: three-part fp16 records of s2 W2 ([k-step][part][64], rows
-  // past D zero)
+  // mlp.fold: three-part fp16 records of W2, every row times a power of two
+  // of its own ([k-step][part][64], rows past D zero), and those powers'
+  // inverses ([32])
   const void *w2r = nullptr;
-  float s2 = 1.f;
+  const float *s2inv = nullptr;
   float *z = nullptr;  // [n][D]
   bool z16 = false;    // set by launch_embed
 };

@@ -35,7 +35,9 @@ constexpr int MAX_D = 16;
 
 // Parts of the output layer's split products: with x = x1 + x2 + x3 and
 // w = w1 + w2 + w3 in fp16 (33 bits each), the six products of order up to
-// 2^-22 leave an error below fp32's own rounding.
+// 2^-22 leave an error below fp32's own rounding.  (Rows of W2 that their
+// scales do not keep clear of fp16's subnormal floor are not folded:
+// row_scale() in gnn_api.hip.)
 constexpr int OUT_PARTS = 3;
 
 template <int MB, bool SPLIT, bool FOLD, int FK>
@@ -46,8 +48,9 @@ __global__ __launch_bounds__(64 * SM_WAVES) void embed_mlp(EmbedArgs a) {
   constexpr int NOUT = 2 * MB * OUT_PARTS * 64;
   __shared__ typename M::Lds lds;
   __shared__ h8 out_r[FOLD ? NOUT : 1];
-  __shared__ float out_w[FOLD ? 1 : MAX_D * H];
-  __shared__ float out_b[32];
+  __shared__ alignas(16) float out_w[FOLD ? 1 : MAX_D * H];
+  __shared__ alignas(16) float out_b[32];
+  __shared__ alignas(16) float out_s[32];
   const int lane = threadIdx.x & 63, hh = lane >> 5, n = lane & 31;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int F = FK ? FK : a.F;
@@ -67,6 +70,7 @@ __global__ __launch_bounds__(64 * SM_WAVES) void embed_mlp(EmbedArgs a) {
   M::load(lds, a.mlp);
   if constexpr (FOLD) {
     for (int i = threadIdx.x; i < NOUT; i += 64 * SM_WAVES) out_r[i] = ((const h8 *)a.w2r)[i];
+    if (threadIdx.x < 32) out_s[threadIdx.x] = a.s2inv[threadIdx.x];
   } else {
     for (int i = threadIdx.x; i < a.D * H; i += 64 * SM_WAVES) out_w[i] = a.w2[i];
   }
@@ -117,13 +121,12 @@ __global__ __launch_bounds__(64 * SM_WAVES) void embed_mlp(EmbedArgs a) {
       }
 #pragma unroll
       for (int v = 0; v < 16; ++v) z[v] += zl[v];
-      const float inv = 1.f / a.s2;  // a power of two
       if (row < a.n) {
 #pragma unroll
         for (int q = 0; q < MAX_D / 8; ++q) {
           const int d0 = 8 * q + 4 * hh;
           float *o = a.z + row * a.D + d0;
-          const f4 v = f4{z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]} * inv +
+          const f4 v = f4{z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]} * *(const f4 *)(out_s + d0) +
                        *(const f4 *)(out_b + d0);
           if (d0 + 4 <= a.D && a.z16) {
             *(f4 *)o = v;

@@ -66,7 +66,7 @@ struct SmallMlp {
   struct Lds {
     h8 rec[NREC];           // layer 1: f16x2 records of s1 W1
     float w0[KS * MB * 64];  // layer 0: [step][mb][lane], W0[32 mb + lane % 32][2 step + lane / 32]
-    float prm[6 * H];        // b0 g0 beta0 | s1 b1, g1, beta1 (FOLD: g unused)
+    alignas(16) float prm[6 * H];  // b0 g0 beta0 | s1 b1, g1, beta1 (FOLD: g unused)
   };
 
   static __device__ __forceinline__ void load(Lds &s, const SmallMlpArgs &a) {

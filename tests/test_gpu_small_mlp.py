@@ -99,3 +99,67 @@ def test_embedding_widths_and_gains(G, oracle_mod, F, H, D, n, kind):
     ref = oracle_mod.embed(w, x, H, D)
     # sums of H fp32 terms of O(1): a few 2^-24 sqrt(H) |z|, far below 1e-5
     np.testing.assert_allclose(z, ref, rtol=0, atol=1e-5 * max(1.0, np.abs(ref).max()))
+
+
+def embed_exact(w, x, F, H, D):
+    """z, and per output the sum of its terms' magnitudes, in 64 bits."""
+    p = {k: torch.as_tensor(v.astype(np.float64)) for k, v in I.embed_blob_views(w, F, H, D).items()}
+    a = torch.as_tensor(x.astype(np.float64))
+    for k in ("embed.0", "embed.1"):
+        y = a @ p[k + ".W"].T + p[k + ".b"]
+        y = torch.nn.functional.layer_norm(y, (H,), p[k + ".g"], p[k + ".beta"], 1e-5)
+        a = torch.relu(y)
+    W, b = p["embed.2.W"], p["embed.2.b"]
+    return (a @ W.T + b).numpy(), (a @ W.abs().T + b.abs()).numpy()
+
+
+@pytest.mark.parametrize("kind", ["rows", "tiny_rows", "huge_gain", "huge_rows", "one_large_entry",
+                                  "tiny_layer", "huge_hidden"])
+@pytest.mark.parametrize("H", [64, 128])
+def test_embedding_output_rows_of_any_size(G, H, kind):
+    """Every output keeps fp32's precision whatever the sizes of its row, of
+    the other rows and of the gains that are folded into it."""
+    F, D, n = 3, 8, 4001
+    rng = np.random.default_rng(H)
+    x = rng.normal(size=(n, F)).astype(np.float32)
+    w = I.make_embed_weights(F, H, D, 13, affine_noise=0.3)
+    v = I.embed_blob_views(w, F, H, D)
+    W, b = v["embed.2.W"], v["embed.2.b"]
+    b *= 1e-3
+    if kind == "rows":
+        s = 2.0 ** -np.array([0, 4, 12, 16, 20, 24, 28, 32])
+        W *= s[:, None]
+        b *= s
+    elif kind == "tiny_rows":
+        s = 2.0 ** -np.array([0, 45, 60, 80, 100, 0, 1, 2])
+        W *= s[:, None]
+        b *= s
+    elif kind == "huge_gain":  # |g| W past 2^56
+        v["embed.1.g"][:] *= 1e20
+        v["embed.1.beta"][:] *= 1e20
+    elif kind == "huge_rows":
+        W[1] *= 1e25
+        W[3] *= 2.0 ** 110
+    elif kind == "one_large_entry":  # ... of a feature that is never active
+        v["embed.1.beta"][7] = -40.0 * abs(v["embed.1.g"][7])
+        W[:, 7] *= 2.0 ** np.array([0, 8, 14, 18, 22, 26, 30, 34])
+    elif kind == "tiny_layer":
+        W *= 2.0 ** -70
+        b *= 2.0 ** -70
+    elif kind == "huge_hidden":  # layer 1 times the first gains leaves its records' scale
+        v["embed.0.g"][:] *= 1000.0
+        v["embed.1.W"][:] *= 2.0 ** 57
+        v["embed.1.b"][:] = 0.0
+    m = G.Embedder(w, G.make_embed_dims(F, H, D))
+    try:
+        z = m(dev(x)).cpu().numpy().astype(np.float64)
+    finally:
+        m.close()
+    ref, mag = embed_exact(w, x, F, H, D)
+    # the hidden outputs' own error (about 1e-6 of the largest, under the
+    # parity bound 1e-5) times the terms' magnitudes; the largest terms also
+    # cover points where few features are active
+    scale = np.maximum(mag, mag.max(axis=0, keepdims=True) * 1e-1)
+    err = np.abs(z - ref) / scale
+    assert np.isfinite(z).all()
+    assert err.max() <= 1e-5, err.max(axis=0)

@@ -418,6 +418,7 @@ struct gnn_handle {
     hipEvent_t done;
     hipStream_t last;
     bool busy, recorded;
+    bool captured;  // the last call was captured: `done` is a graph's, not to be queried
   };
   std::mutex ws_mu;
   std::vector<WsEntry> ws;
@@ -732,6 +733,65 @@ int ws_check_limit(gnn_handle *h, size_t more) {
   return GNN_OK;
 }
 
+// Whether `stream` is being captured (or, for the null stream, may not be
+// touched because another one is).
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+// The process's handles, for gpu_shared.  The lock is taken before a handle's
+// ws_mu, never inside it.  Never destroyed: handles may live in a program's
+// own statics.
+struct Handles {
+  std::mutex mu;
+  std::vector<gnn_handle *> all;
+};
+Handles &handles() {
+  static Handles &h = *new Handles;
+  return h;
+}
+
+// Whether another inference of this process is being issued, or not known to
+// have finished, on another stream of h's device: the launches of a small
+// event then leave it the CUs they can (NodeArgs::pack).  `slot` is the
+// caller's own entry of h.  Only a hint: any answer gives the same results.
+bool gpu_shared(gnn_handle *h, int slot, hipStream_t stream) {
+  std::lock_guard<std::mutex> all(handles().mu);
+  bool may_query = false, asked = false;
+  for (gnn_handle *o : handles().all) {
+    if (o->device != h->device) continue;
+    std::unique_lock<std::mutex> lk(o->ws_mu, std::try_to_lock);
+    if (!lk) return true;  // a call is being issued there
+    for (int i = 0; i < (int)o->ws.size(); ++i) {
+      const auto &e = o->ws[i];
+      if ((o == h && i == slot) || !e.base) continue;
+      if (e.busy) return true;
+      if (!e.recorded || e.captured || e.last == stream) continue;
+      if (!asked) may_query = !capturing(stream);  // no query into a capture
+      asked = true;
+      if (!may_query) continue;
+      // ... nor one that breaks another thread's
+      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+      if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
+        (void)hipGetLastError();
+        continue;
+      }
+      const hipError_t q = hipEventQuery(e.done);
+      (void)hipThreadExchangeStreamCaptureMode(&mode);
+      if (q != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+      }
+    }
+  }
+  return false;
+}
+
 // Most cached workspaces per handle; beyond this, calls share entries
 // (ordered by events) rather than allocate more.
 constexpr size_t kMaxCachedWorkspaces = 16;
@@ -811,7 +871,7 @@ int ws_acquire(gnn_handle *h, size_t bytes, hipStream_t stream, void **base, int
       pick = victim;
     } else {
       if (const int lr = ws_check_limit(h, ws_round(bytes))) return lr;
-      gnn_handle::WsEntry e{nullptr, 0, nullptr, stream, false, false};
+      gnn_handle::WsEntry e{nullptr, 0, nullptr, stream, false, false, false};
       if (hipEventCreateWithFlags(&e.done, hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError();
         return fail(GNN_E_HIP, "hipEventCreate for a workspace failed");
@@ -857,6 +917,7 @@ int ws_release(gnn_handle *h, int slot, void *base, size_t bytes, hipStream_t st
   std::lock_guard<std::mutex> lk(h->ws_mu);
   auto &e = h->ws[slot];
   int rc = GNN_OK;
+  e.captured = capturing(stream);
   if (hipEventRecord(e.done, stream) == hipSuccess) {
     e.recorded = true;
   } else {  // no event to wait for: finish the call's work here instead
@@ -880,7 +941,7 @@ struct RunOut {
   // cache (no allocation, no profiling events): the no-allocation entry point.
   void *ext_base = nullptr;
   size_t ext_bytes = 0;
-  bool pack = false;  // NodeArgs::pack
+  bool pack = false;  // NodeArgs::pack, also when no other call is in flight yet
 };
 
 int run(gnn_handle *hd, const float *x, const int32_t *ei, int64_t N, int64_t E,
@@ -907,6 +968,7 @@ int run(gnn_handle *hd, const float *x, const int32_t *ei, int64_t N, int64_t E,
   const bool fused = fac && hd->fd.split;
   w.bytes = plan_workspace(w, N, E, H, ab, fac, fused);
   int slot = -1;
+  bool pack = ro.pack;
   if (ro.ext_base) {
     if (w.bytes > ro.ext_bytes)
       return fail(GNN_E_INVALID_ARG,
@@ -919,6 +981,11 @@ int run(gnn_handle *hd, const float *x, const int32_t *ei, int64_t N, int64_t E,
     if (rc != GNN_OK) return rc;
   }
   plan_workspace(w, N, E, H, ab, fac, fused);
+  // (looked up only where the launch rules ask for it: within a round of the
+  // edge kernels, or four units of the node kernels per CU)
+  if (fused && !pack && !ro.csr_only && ((E + 31) / 32 < 16 * (int64_t)hd->fd.grid_upd ||
+                                (N + 31) / 32 <= 4 * (int64_t)hd->fd.grid_node))
+    pack = gpu_shared(hd, slot, stream);
   if (!w.csr.status) {  // (never: see plan_workspace)
     rc = fail(GNN_E_UNSUPPORTED, "no room for the CSR sort's counters");
     goto out;
@@ -975,7 +1042,7 @@ int run(gnn_handle *hd, const float *x, const int32_t *ei, int64_t N, int64_t E,
     na.nchunks = fd.enc_chunks;
     na.s2 = fd.s2_ne;
     na.nproj = 2;
-    na.pack = ro.pack;
+    na.pack = pack;
     // with no iteration h0 feeds the classifier only through pb
     na.h_out = T == 0 && ro.stop_iter < 0 ? nullptr : (float *)w.h;
     na.p_out[0] = w.pa;
@@ -1019,7 +1086,7 @@ int run(gnn_handle *hd, const float *x, const int32_t *ei, int64_t N, int64_t E,
       ea.g2 = m.l1.g;
       ea.beta2 = m.l1.beta;
       ea.eps = d.ln_eps;
-      ea.pack = ro.pack;
+      ea.pack = pack;
       return ea;
     };
     auto launch_edge = [&](EdgeMode mode, const EdgeArgs &ea, int grid) {
@@ -1100,7 +1167,7 @@ int run(gnn_handle *hd, const float *x, const int32_t *ei, int64_t N, int64_t E,
         nu.row_bound = fd.row_bound;
       }
       nu.nproj = 1;
-      nu.pack = ro.pack;
+      nu.pack = pack;
       // In place: a wave reads its rows before writing them.  The last
       // update's h reaches the classifier only through its projections, so
       // it is not stored unless the stages are being exported.
@@ -1647,6 +1714,10 @@ gnn_handle *gnn_create(const float *weights, const gnn_dims *dims) {
     }
     fd.grid_node = node_f32_grid(n_cu);
   }
+  {
+    std::lock_guard<std::mutex> lk(handles().mu);
+    handles().all.push_back(h);
+  }
   return h;
 }
 
@@ -1681,6 +1752,11 @@ int gnn_set_workspace_limit(gnn_handle *h, int64_t bytes) {
 
 void gnn_destroy(gnn_handle *h) {
   if (!h) return;
+  {
+    std::lock_guard<std::mutex> lk(handles().mu);
+    auto &v = handles().all;
+    v.erase(std::remove(v.begin(), v.end(), h), v.end());
+  }
   {
     DeviceGuard guard(h->device);
     (void)hipDeviceSynchronize();

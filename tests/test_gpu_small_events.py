@@ -47,3 +47,104 @@ def test_spread_and_packed_launches_agree(oracle_mod, dtype, flags, hidden):
     finally:
         s.close()
         m.close()
+
+
+@pytest.mark.parametrize("dtype,flags", DTYPES)
+def test_concurrent_calls_leave_each_other_cus(dtype, flags):
+    """Four threads that call one model, or a model each, on streams of their
+    own take no longer than the queue of four instances, whose launches are
+    always packed, does for the same 16 events (spread over the CUs, each
+    event's launches hold back the others': 1.33 times as long in fp32 and
+    bf16; packed, 0.91 at most)."""
+    import threading
+    import time
+
+    from paper_2402_09633_amd import gnn as G
+    from paper_2402_09633_amd import inputs as I
+
+    w = I.make_weights(3, 128, 1, 5, affine_noise=0.1)
+    dims = G.make_dims(3, 128, 8, dtype=G.GNN_BF16 if dtype == "bf16" else G.GNN_FP32, flags=flags)
+    models = [G.Model(w, dims) for _ in range(4)]
+    server = G.Server(models[0], 4)
+    graphs = [I.uniform_graph(10_000, 30_000, seed=80 + k) for k in range(4)]
+    ev = [(dev(g.x), dev(g.edge_index)) for g in graphs]
+    out = [torch.empty(30_000, device="cuda") for _ in ev]
+    streams = [torch.cuda.Stream() for _ in ev]
+    torch.cuda.synchronize()
+
+    def queue():
+        for i in [server.submit(*ev[k % 4], out[k % 4]) for k in range(16)]:
+            server.wait(i)
+
+    def threads(ms):
+        def work(k):
+            for _ in range(4):
+                ms[k](*ev[k], out=out[k], stream=streams[k])
+                streams[k].synchronize()
+        ts = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+        for t in ts:
+            t.start()
+        for t in ts:
+            t.join()
+
+    ways = [queue, lambda: threads([models[0]] * 4), lambda: threads(models)]
+    best = [1e9] * 3
+    try:
+        refs = []
+        for k in range(4):
+            refs.append(models[k](*ev[k]).clone())
+        for _ in range(8):
+            for i, f in enumerate(ways):
+                t = time.perf_counter()
+                f()
+                torch.cuda.synchronize()
+                best[i] = min(best[i], time.perf_counter() - t)
+                for o, ref in zip(out, refs):
+                    assert torch.equal(o, ref)
+        assert max(best[1:]) <= 1.1 * best[0], best
+    finally:
+        server.close()
+        for m in models:
+            m.close()
+
+
+def test_capture_beside_running_calls():
+    """Looking for other calls breaks no capture, this thread's or another's:
+    a call is captured while one of another model runs, and one is issued by
+    another thread while the capture is open."""
+    import threading
+
+    from paper_2402_09633_amd import gnn as G
+    from paper_2402_09633_amd import inputs as I
+
+    w = I.make_weights(3, 128, 1, 5, affine_noise=0.1)
+    a, b = (G.Model(w, G.make_dims(3, 128, 2)) for _ in range(2))
+    g, big = I.uniform_graph(2_000, 8_000, seed=1), I.uniform_graph(40_000, 150_000, seed=2)
+    x, ei, bx, bei = dev(g.x), dev(g.edge_index), dev(big.x), dev(big.edge_index)
+    out, bout = torch.zeros(8_000, device="cuda"), torch.zeros(150_000, device="cuda")
+    side, cap, other = (torch.cuda.Stream() for _ in range(3))
+    try:
+        ref, bref = a(x, ei).clone(), b(bx, bei).clone()
+        b(x, ei, out=torch.empty(8_000, device="cuda"), stream=other)  # a second workspace of b's
+        G.gnn_infer_noalloc(a.handle, x, ei, 2_000, 8_000, out)  # (looks up its scratch)
+        torch.cuda.synchronize()
+        out.zero_()
+        out2 = torch.zeros(8_000, device="cuda")
+        torch.cuda.synchronize()
+        b(bx, bei, out=bout, stream=side)  # in flight while the capture looks
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=cap, capture_error_mode="thread_local"):
+            G.gnn_infer_noalloc(a.handle, x, ei, 2_000, 8_000, out, cap)
+            t = threading.Thread(target=lambda: b(x, ei, out=out2, stream=other))
+            t.start()
+            t.join()
+        torch.cuda.synchronize()
+        assert torch.equal(bout, bref) and torch.equal(out2, ref)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref)
+    finally:
+        a.close()
+        b.close()

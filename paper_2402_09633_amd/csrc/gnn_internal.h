@@ -320,11 +320,10 @@ struct FrnnArgs {
   // ([n][D - 4], D > 4)
   float *z4 = nullptr, *zr = nullptr;
   float *z2 = nullptr;        // coordinates 3 and 4 ([n + 4][2], D > 4)
-  // [n][n_slots], by id: a point's partners, or, of one with more than
-  // n_slots (a multiple of 4), its bucket position
-  int32_t *slots = nullptr;
-  int32_t n_slots = 0;
-  int32_t *count = nullptr;   // [n] pairs per point
+  int32_t *slots = nullptr;   // [n][n_slots], by id: a point's first partners
+  int32_t n_slots = 0;        // a multiple of 4
+  int32_t *again = nullptr;   // per workgroup of the collecting launch: any point to scan again
+  int32_t *count = nullptr;   // [n] pairs per point, and a flag (graph.hip)
   int64_t *offs = nullptr;    // [n] exclusive offsets
   int64_t *bsum = nullptr;    // [frnn_scan_blocks(n)] scan scratch
   int64_t *total = nullptr;   // device: number of pairs (row stride of out)

@@ -231,11 +231,20 @@ __global__ __launch_bounds__(FTHREADS) void frnn_gather(FrnnArgs a, bool vec) {
 // candidates a load; with fewer, on the first four, 16 bytes.  Only the
 // survivors' other coordinates and ids are read, and those later, from a list
 // in LDS, LIST at a time: done where they are found, one lane's survivor makes
-// the whole wave wait for its loads.  Candidates are taken U at a time and the
-// next three cells' bounds are requested ahead.
-constexpr int LIST = 16;
-template <int D, typename Emit>
-__device__ __forceinline__ void scan_point(const FrnnArgs &a, int64_t p, int32_t i, Emit emit) {
+// the whole wave wait for its loads.  The lanes empty their lists together
+// when one is full; each for itself, the wave waited for the loads of one lane
+// after the other where the two coordinates separate nothing (both constant,
+// 300k points: 735 us, together 440; without a first test 490).  Lists of 24:
+// of 16 are full too often (1.0M points 390 against 370 us for the launch), of
+// 32 cost a workgroup per CU (300k points 98 -> 139 us).  Candidates are taken
+// U at a time and the next three cells' bounds are requested ahead.
+//
+// direct: no first test, every candidate's id and coordinates read at once.
+// AGAIN: compiled for direct only.
+constexpr int LIST = 24;
+template <int D, bool AGAIN, typename Emit>
+__device__ __forceinline__ void scan_point(const FrnnArgs &a, int64_t p, int32_t i, bool direct,
+                                           Emit emit) {
   constexpr int U = 4;
   constexpr bool PAIRS = D >= 5;
   typedef int32_t i2 __attribute__((ext_vector_type(2), aligned(4)));
@@ -243,9 +252,32 @@ __device__ __forceinline__ void scan_point(const FrnnArgs &a, int64_t p, int32_t
   constexpr int NY = D > 1 ? 3 : 1, NZ = D > 2 ? 3 : 1;
   const f4 *z4 = (const f4 *)a.z4;
   const f4 zi = z4[p];
-  float zri[D > 4 ? D - 4 : 1];
+  // coordinates from the fifth on of the point at bucket position q
+  auto load_rest = [&](int64_t q, float (&v)[D > 4 ? D - 4 : 1]) {
+    if constexpr (D > 4 && D % 4 == 0) {
 #pragma unroll
-  for (int k = 4; k < D; ++k) zri[k - 4] = a.zr[p * (D - 4) + k - 4];
+      for (int k = 0; k < D - 4; k += 4) {
+        const f4 w = *(const f4 *)(a.zr + q * (D - 4) + k);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[k + t] = w[t];
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < D - 4; ++k) v[k] = a.zr[q * (D - 4) + k];
+    }
+  };
+  float zri[D > 4 ? D - 4 : 1];
+  load_rest(p, zri);
+  auto dist2 = [&](const f4 &v, const float (&w)[D > 4 ? D - 4 : 1]) {
+    float acc = 0.f;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      const float t = k < 4 ? zi[k < 4 ? k : 0] - v[k < 4 ? k : 0]
+                            : zri[k < 4 ? 0 : k - 4] - w[k < 4 ? 0 : k - 4];
+      acc = __builtin_fmaf(t, t, acc);
+    }
+    return acc;
+  };
   int ci[3];
   {
     const float zc[3] = {zi[0], zi[1], zi[2]};
@@ -293,32 +325,58 @@ __device__ __forceinline__ void scan_point(const FrnnArgs &a, int64_t p, int32_t
         for (int e = 0; e < c; ++e) qe[x] = key_of(e) == key ? qb[x] : qe[x];
     }
   };
+  if (direct) {
+    for (int c = 0; c < 3 * NY * NZ; ++c) {
+      const uint32_t key = key_of(c);
+      const i2 b = *(const i2 *)(a.rp + key);
+      bool seen = false;
+      if (collide)
+        for (int e = 0; e < c; ++e) seen |= key_of(e) == key;
+      if (seen) continue;
+      for (int32_t q0 = b[0]; q0 < b[1]; q0 += U) {
+        int32_t j[U];
+        f4 zq[U];
+        float zrq[U][D > 4 ? D - 4 : 1];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {  // (past the bucket's end: its last point again)
+          const int32_t q = q0 + u < b[1] ? q0 + u : b[1] - 1;
+          j[u] = a.perm[q];
+          if constexpr (D >= 4) {
+            zq[u] = z4[q];
+          } else {  // (what the lanes get back bounds a scan of shared buckets)
+#pragma unroll
+            for (int k = 0; k < D; ++k) zq[u][k] = a.z4[4 * (int64_t)q + k];
+          }
+          load_rest(q, zrq[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (q0 + u < b[1] && j[u] > i && dist2(zq[u], zrq[u]) < a.r2) emit(j[u]);
+      }
+    }
+    return;
+  }
+  if constexpr (AGAIN) return;
   __shared__ int32_t list[LIST][FTHREADS];
   int n_list = 0;
+  // (one entry at a time: two or four cost the registers of a wave per SIMD,
+  // 300k points 238 -> 270 us for the call)
   auto flush = [&]() {
     for (int k = 0; k < n_list; ++k) {
       const int32_t q = list[k][threadIdx.x];
       const int32_t j = a.perm[q];
-      float acc = 0.f;
+      bool near = true;
       if constexpr (PAIRS) {  // (else the list holds only pairs)
-        const f4 zq = z4[q];
-        float zrq[D > 4 ? D - 4 : 1];
-#pragma unroll
-        for (int c = 4; c < D; ++c) zrq[c - 4] = a.zr[(int64_t)q * (D - 4) + c - 4];
-#pragma unroll
-        for (int c = 0; c < D; ++c) {
-          const float t = c < 4 ? zi[c < 4 ? c : 0] - zq[c < 4 ? c : 0] : zri[c < 4 ? 0 : c - 4] - zrq[c < 4 ? 0 : c - 4];
-          acc = __builtin_fmaf(t, t, acc);
-        }
+        float w[D > 4 ? D - 4 : 1];
+        load_rest(q, w);
+        near = dist2(z4[q], w) < a.r2;
       }
-      if ((!PAIRS || acc < a.r2) && j > i) emit(j);
+      if (near && j > i) emit(j);
     }
     n_list = 0;
   };
   auto push = [&](int32_t q) {
-    if (q == p) return;
-    if (n_list == LIST) flush();
-    list[n_list++][threadIdx.x] = q;
+    if (q != p) list[n_list++][threadIdx.x] = q;
   };
   struct Batch {
     f4 v[PAIRS ? U / 2 : U];
@@ -336,6 +394,7 @@ __device__ __forceinline__ void scan_point(const FrnnArgs &a, int64_t p, int32_t
     }
   };
   auto test = [&](const Batch &w, int32_t q0, int32_t qe) {
+    if (__any(n_list > LIST - U)) flush();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       bool near;
@@ -383,24 +442,65 @@ __device__ __forceinline__ void scan_point(const FrnnArgs &a, int64_t p, int32_t
   flush();
 }
 
+// Whether the point at bucket position p has one `step` places on in its
+// bucket that the first test lets through.
+template <int D>
+__device__ __forceinline__ bool dense_at(const FrnnArgs &a, int64_t p, int step) {
+  const f4 z = ((const f4 *)a.z4)[p];
+  const float zc[3] = {z[0], z[1], z[2]};
+  int ci[3];
+  cell_of(zc, D < 3 ? D : 3, a.inv_cell, ci);
+  const uint32_t key = cell_hash(ci, a.mask);
+  bool near = (threadIdx.x & 63) + step < 64 && __shfl_down(key, step) == key;
+  if constexpr (D >= 5) {
+    const float z_4 = a.z2[2 * p + 1];
+    const float t3 = z[3] - __shfl_down(z[3], step), t4 = z_4 - __shfl_down(z_4, step);
+    near = near && t3 * t3 < a.r2 && t4 * t4 < a.r2;
+  } else {
+    float d2 = 0.f;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+      const float t = z[k] - __shfl_down(z[k], step);
+      d2 = __builtin_fmaf(t, t, d2);
+    }
+    near = near && d2 < a.r2;
+  }
+  return near;
+}
+
 // Pairs of every point: the count, and up to a.n_slots partners.  Thread
 // p handles the point at bucket position p (neighbouring threads handle
 // neighbouring points, whose candidates they share in the caches).  Notes in
 // a.again whether points of the workgroup have to be scanned again.
+//
+// In groups of points that are all near one another the first test rejects
+// too little to pay.  A workgroup where DENSE_LANES points have a partner by
+// the first test DENSE_STEP places on in their bucket (groups of about 40 and
+// more in few cells) does without it; where MANY_LANES have one MANY_STEP
+// places on, most points have more partners than slots, and it only counts.
+// Whole call, us, test and slots for all -> without the test -> only counting,
+// 100k points, 8 dimensions: groups of 20 255 -> 270 -> 335, of 60 (width
+// 0.005) 540 -> 510 -> 490, of 100 600 -> 515 -> 497, of 250 1000 -> 820 -> 770;
+// 300k points in groups of 10 stay with the test (235; 445 without).
+constexpr int DENSE_STEP = 4, DENSE_LANES = 7 * FTHREADS / 16;
+constexpr int MANY_STEP = 16, MANY_LANES = FTHREADS / 4;
 template <int D>
-__global__ __launch_bounds__(FTHREADS) void frnn_collect(FrnnArgs a) {
+__global__ __launch_bounds__(FTHREADS, D >= 5 && D <= 10 ? 5 : 4) void frnn_collect(FrnnArgs a) {
   const int64_t p = (int64_t)blockIdx.x * FTHREADS + threadIdx.x;
+  const bool in = p < a.n;
+  const bool dense = __syncthreads_count(in && dense_at<D>(a, p, DENSE_STEP)) >= DENSE_LANES;
+  const bool many = dense && __syncthreads_count(in && dense_at<D>(a, p, MANY_STEP)) >= MANY_LANES;
   int32_t cnt = 0;
-  if (p < a.n) {
+  if (in) {
     const int32_t i = a.perm[p];
     int32_t *slot = a.slots + (int64_t)i * a.n_slots;
-    scan_point<D>(a, p, i, [&](int32_t j) {
-      if (cnt < a.n_slots) slot[cnt] = j;
+    scan_point<D, false>(a, p, i, dense, [&](int32_t j) {
+      if (!many && cnt < a.n_slots) slot[cnt] = j;
       ++cnt;
     });
-    a.count[i] = cnt > a.n_slots ? cnt | FRNN_AGAIN : cnt;
+    a.count[i] = many || cnt > a.n_slots ? cnt | FRNN_AGAIN : cnt;
   }
-  const int again = __syncthreads_or(cnt > a.n_slots);
+  const int again = __syncthreads_or(many || cnt > a.n_slots);
   if (threadIdx.x == 0) a.again[blockIdx.x] = again;
 }
 
@@ -408,9 +508,10 @@ __global__ __launch_bounds__(FTHREADS) void frnn_collect(FrnnArgs a) {
 // the workgroups scans a second time, in bucket order like the first, the
 // points whose partners were not all collected (in the order of the ids a
 // wave's lanes share nothing: 100k points in groups of 100, 1060 us against
-// 220); the second half writes the collected partners of the others in the
-// order of the ids, so that neighbouring threads write neighbouring pairs (in
-// bucket order every store had a line of its own: 40 us against 9).
+// 220), without the first test: they have many partners.  The second half
+// writes the collected partners of the others in the order of the ids, so
+// that neighbouring threads write neighbouring pairs (in bucket order every
+// store had a line of its own: 40 us against 9).
 template <int D>
 __global__ __launch_bounds__(FTHREADS) void frnn_write(FrnnArgs a, unsigned half) {
   const int64_t total = *a.total;
@@ -429,7 +530,7 @@ __global__ __launch_bounds__(FTHREADS) void frnn_write(FrnnArgs a, unsigned half
     ++o;
   };
   if (again) {
-    scan_point<D>(a, k, (int32_t)i, put);
+    scan_point<D, true>(a, k, (int32_t)i, true, put);
   } else {
     typedef int32_t i4 __attribute__((ext_vector_type(4)));
     const int32_t *slot = a.slots + i * a.n_slots;

@@ -92,3 +92,47 @@ def test_writing_many_partners_takes_one_more_scan(dim):
     count = best_time(lambda: G.gnn_frnn(z, n, dim, r2))
     full = best_time(lambda: G.gnn_frnn(z, n, dim, r2, out, c))
     assert full <= 2.4 * count, (full, count)
+
+
+@pytest.mark.parametrize("still", [(3, 4), (3, 4, 5, 6, 7)])
+def test_coordinates_that_separate_nothing(still):
+    """Where the coordinates of the first test are constant every candidate
+    passes it; the search then costs 1.9 times what it does with other
+    coordinates constant (its lists emptied lane by lane: 3 times)."""
+    from paper_2402_09633_amd import gnn as G
+    n, r2 = 300_000, 0.02 ** 2
+    z = I.clustered_points(n, 8, 3, sigma=0.005)
+    moved = z.copy()
+    moved[:, 6:] = 0.25
+    z[:, list(still)] = 0.25
+    t = []
+    for p in (z, moved):
+        zd = torch.as_tensor(p).cuda()
+        c = G.gnn_frnn(zd, n, 8, r2)
+        out = torch.empty(2 * c, dtype=torch.int32, device="cuda")
+        t.append(best_time(lambda: G.gnn_frnn(zd, n, 8, r2, out, c)))
+    assert t[0] <= 2.4 * t[1], t
+
+
+@pytest.mark.parametrize("dim", [1, 2, 3, 4, 5, 8, 10, 16])
+@pytest.mark.parametrize("size", [8, 40, 90, 300])
+def test_groups_of_all_sizes(oracle_mod, dim, size):
+    """Around the limits between testing first, scanning at once and only
+    counting, mixed with single points, and a last workgroup of one point."""
+    from paper_2402_09633_amd import gnn as G
+    r = 0.02 if dim > 2 else 0.0005
+    z = groups(1793, size, dim, r / 8, size + dim).cpu().numpy()
+    rng = np.random.default_rng(dim)
+    z[rng.integers(0, 1793, 300)] = rng.random((300, dim)).astype(np.float32)
+    r2 = float(np.float32(r) ** 2)
+    ref = pair_set(oracle_mod.frnn(z, r2).T)
+    zd = torch.as_tensor(z).cuda()
+    c = G.gnn_frnn(zd, 1793, dim, r2)
+    assert c == len(ref)
+    out = torch.full((2 * c + 1,), -5, dtype=torch.int32, device="cuda")
+    G.gnn_frnn(zd, 1793, dim, r2, out, c)
+    got = out.cpu().numpy()
+    assert got[-1] == -5
+    ei = got[:-1].reshape(2, c)
+    assert pair_set(ei) == ref
+    assert (np.diff(ei[0]) >= 0).all()

@@ -445,6 +445,18 @@ int gnn_debug_stages(gnn_handle *h, const float *node_feat, const int32_t *edge_
                      int64_t n_nodes, int64_t n_edges, int32_t stop_iter, float *h_out,
                      float *e_out, float *agg_in_out, float *agg_out_out, hipStream_t stream);
 
+/* gnn_frnn with the limits that depend on its size: n_slots, the partners
+ * kept per point by the first scan (4, 8 .. 32; a point with more is scanned
+ * twice), and scan_direct (0..4096), the count tiles up to which the scan has
+ * no launch of its own over their sums.  The same pairs in the same order. */
+int gnn_debug_frnn(const float *z, int64_t n_nodes, int32_t dim, float r2, int32_t *edge_index,
+                   int64_t max_pairs, int64_t *n_pairs, int32_t n_slots, int64_t scan_direct,
+                   hipStream_t stream);
+
+/* Workspace of such a call in bytes (0: bad arguments).  gnn_frnn takes 32
+ * slots up to 2^24 points where they can be allocated, else 4. */
+size_t gnn_debug_frnn_bytes(int64_t n_nodes, int32_t dim, int32_t n_slots);
+
 #ifdef __cplusplus
 }
 #endif

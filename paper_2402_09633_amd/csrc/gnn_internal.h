@@ -326,6 +326,7 @@ struct FrnnArgs {
   int32_t *count = nullptr;   // [n] pairs per point, and a flag (graph.hip)
   int64_t *offs = nullptr;    // [n] exclusive offsets
   int64_t *bsum = nullptr;    // [frnn_scan_blocks(n)] scan scratch
+  int64_t scan_direct = 0;    // scans of up to that many blocks without a launch over bsum
   int64_t *total = nullptr;   // device: number of pairs (row stride of out)
   int32_t *out = nullptr;     // [2][total], written when total <= max_pairs; or nullptr
   int64_t max_pairs = 0;

@@ -33,6 +33,11 @@ namespace {
 constexpr int FTHREADS = 256;
 constexpr int MAX_D = 16;
 
+// Slots of a point in the pair search.  The fewest take no memory of their
+// own: a sort pass leaves 16 bytes a point.
+constexpr int32_t FRNN_SLOTS_LEAST = 4, FRNN_SLOTS_MOST = 32;
+static_assert(FRNN_SLOTS_LEAST * sizeof(int32_t) == 2 * sizeof(uint2), "slots in place of pairs");
+
 // Parts of the output layer's split products: with x = x1 + x2 + x3 and
 // w = w1 + w2 + w3 in fp16 (33 bits each), the six products of order up to
 // 2^-22 leave an error below fp32's own rounding.  (Rows of W2 that their
@@ -702,7 +707,7 @@ hipError_t launch_frnn_pairs(const FrnnArgs &a, hipStream_t stream) {
   if (e == hipSuccess) e = launch_points<false>(a, stream);
   if (e != hipSuccess) return e;
   const unsigned nb = (unsigned)frnn_scan_blocks(a.n);
-  const bool direct = nb <= SCAN_DIRECT;
+  const bool direct = nb <= a.scan_direct;
   if ((e = launch(scan_tiles, nb, ST, 0, stream, a.count, a.n, a.bsum))) return e;
   if (!direct)
     if ((e = launch(scan_sums, 1, ST, 0, stream, a.bsum, (int64_t)nb, a.total))) return e;
@@ -725,10 +730,44 @@ size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 }  // namespace
 
-extern "C" int gnn_frnn(const float *z, int64_t n_nodes, int32_t dim, float r2,
-                        int32_t *edge_index, int64_t max_pairs, int64_t *n_pairs,
-                        hipStream_t stream) {
-  using namespace gnn;
+namespace {
+
+using namespace gnn;
+
+// Workspace of one search.
+struct FrnnPlan {
+  uint32_t buckets = 64;
+  size_t bytes = 0;
+  size_t keys, rp, perm, pairs, status, count, offs, total, bsum, z4, zr, z2, slots, again;
+
+  FrnnPlan(int64_t n, int32_t dim, int32_t n_slots) {
+    while ((int64_t)buckets < 2 * n && buckets < (1u << 30)) buckets <<= 1;
+    auto take = [&](size_t b) {
+      const size_t o = bytes;
+      bytes += align256(b > 0 ? b : 1);
+      return o;
+    };
+    keys = take((size_t)n * 4);
+    rp = take(((size_t)buckets + 1) * 4);
+    perm = take((size_t)n * 4);
+    pairs = take((size_t)n * 16);
+    status = take(csr_scratch_bytes(n, buckets, 1));
+    count = take((size_t)n * 4);
+    offs = take((size_t)n * 8);
+    total = take(8);
+    bsum = take(frnn_scan_blocks(n) * 8);
+    z4 = take((size_t)n * 16);
+    zr = dim > 4 ? take((size_t)n * (dim - 4) * 4) : 0;
+    z2 = dim > 4 ? take(((size_t)n + 4) * 8) : 0;  // (read up to 3 points past the end)
+    // few enough, the slots go where the sorted pairs were
+    slots = n_slots <= FRNN_SLOTS_LEAST ? pairs : take((size_t)n * n_slots * 4);
+    again = take((size_t)((n + FTHREADS - 1) / FTHREADS) * 4);
+  }
+};
+
+int frnn(const float *z, int64_t n_nodes, int32_t dim, float r2, int32_t *edge_index,
+         int64_t max_pairs, int64_t *n_pairs, int32_t n_slots, int64_t scan_direct,
+         hipStream_t stream) {
   if (!n_pairs) return set_error(GNN_E_INVALID_ARG, "n_pairs is NULL");
   *n_pairs = 0;
   if (n_nodes < 0 || n_nodes > INT32_MAX)
@@ -746,58 +785,46 @@ extern "C" int gnn_frnn(const float *z, int64_t n_nodes, int32_t dim, float r2,
   a.n = n_nodes;
   a.D = dim;
   a.r2 = r2;
-  // Room for 32 partners a point (a cluster's first point has most of the
-  // cluster; one point that is scanned twice costs the write launch 25 us);
-  // for very many points, whose workspace counts, for 4.
-  a.n_slots = n_nodes <= (1 << 24) ? 32 : 4;
   // Cells a little wider than the radius: a pair that passes the fp32 test
   // differs by less than that along every coordinate.
   const double cell = 1.001 * std::sqrt((double)r2);
   a.inv_cell = std::isfinite(cell) && cell > 0.0 ? (float)(1.0 / cell) : 0.f;
-  uint32_t m = 64;
-  while ((int64_t)m < 2 * n_nodes && m < (1u << 30)) m <<= 1;
-  a.mask = m - 1;
 
   const int64_t n = n_nodes;
-  size_t off = 0;
-  auto take = [&](size_t b) {
-    const size_t o = off;
-    off += align256(b > 0 ? b : 1);
-    return o;
-  };
-  const size_t o_keys = take((size_t)n * 4);
-  const size_t o_rp = take(((size_t)m + 1) * 4), o_perm = take((size_t)n * 4);
-  const size_t o_pa = take((size_t)n * 8), o_pb = take((size_t)n * 8);
-  const size_t o_st = take(csr_scratch_bytes(n, m, 1));
-  const size_t o_cnt = take((size_t)n * 4), o_offs = take((size_t)n * 8), o_total = take(8);
-  const size_t o_bsum = take(frnn_scan_blocks(n) * 8);
-  const size_t o_z4 = take((size_t)n * 16);
-  const size_t o_zr = take(dim > 4 ? (size_t)n * (dim - 4) * 4 : 0);
-  const size_t o_z2 = take(((size_t)n + 4) * 8);  // (read up to 3 points past the end)
-  const size_t o_slots = take((size_t)n * a.n_slots * 4);
-  const size_t o_again = take((size_t)((n + FTHREADS - 1) / FTHREADS) * 4);
+  FrnnPlan w(n, dim, n_slots);
   void *base = nullptr;
-  if (hipMallocAsync(&base, off, stream) != hipSuccess) {
+  hipError_t e = hipMallocAsync(&base, w.bytes, stream);
+  if (e != hipSuccess && n_slots > FRNN_SLOTS_LEAST) {
+    // no room for that many slots: the fewest, and more points scanned twice
+    (void)hipGetLastError();
+    n_slots = FRNN_SLOTS_LEAST;
+    w = FrnnPlan(n, dim, n_slots);
+    e = hipMallocAsync(&base, w.bytes, stream);
+  }
+  if (e != hipSuccess) {
     (void)hipGetLastError();
     return set_error(GNN_E_OOM, "frnn workspace allocation failed");
   }
   unsigned char *b = (unsigned char *)base;
-  int32_t *keys = (int32_t *)(b + o_keys);
+  int32_t *keys = (int32_t *)(b + w.keys);
   CsrScratch cs;
-  cs.pairs_a = (uint2 *)(b + o_pa);
-  cs.pairs_b = (uint2 *)(b + o_pb);
-  cs.status = (uint32_t *)(b + o_st);
-  a.rp = (const int32_t *)(b + o_rp);
-  a.perm = (const int32_t *)(b + o_perm);
-  a.z4 = (float *)(b + o_z4);
-  a.zr = (float *)(b + o_zr);
-  a.z2 = (float *)(b + o_z2);
-  a.slots = (int32_t *)(b + o_slots);
-  a.again = (int32_t *)(b + o_again);
-  a.count = (int32_t *)(b + o_cnt);
-  a.offs = (int64_t *)(b + o_offs);
-  a.total = (int64_t *)(b + o_total);
-  a.bsum = (int64_t *)(b + o_bsum);
+  cs.pairs_a = (uint2 *)(b + w.pairs);
+  cs.pairs_b = cs.pairs_a + n;
+  cs.status = (uint32_t *)(b + w.status);
+  a.mask = w.buckets - 1;
+  a.rp = (const int32_t *)(b + w.rp);
+  a.perm = (const int32_t *)(b + w.perm);
+  a.z4 = (float *)(b + w.z4);
+  a.zr = (float *)(b + w.zr);
+  a.z2 = (float *)(b + w.z2);
+  a.n_slots = n_slots;
+  a.slots = (int32_t *)(b + w.slots);
+  a.again = (int32_t *)(b + w.again);
+  a.count = (int32_t *)(b + w.count);
+  a.offs = (int64_t *)(b + w.offs);
+  a.total = (int64_t *)(b + w.total);
+  a.bsum = (int64_t *)(b + w.bsum);
+  a.scan_direct = scan_direct;
   a.out = edge_index;
   a.max_pairs = max_pairs < INT32_MAX ? max_pairs : INT32_MAX;
 
@@ -805,10 +832,10 @@ extern "C" int gnn_frnn(const float *z, int64_t n_nodes, int32_t dim, float r2,
   // stream does not run dry while the host reads the count.
   int rc = GNN_OK;
   int64_t total = 0;
-  hipError_t e = launch_frnn_keys(a, keys, stream);
+  e = launch_frnn_keys(a, keys, stream);
   if (e == hipSuccess)
-    e = build_buckets(keys, (int32_t)n, (int32_t)m, (int32_t *)(b + o_rp), (int32_t *)(b + o_perm),
-                      cs, stream);
+    e = build_buckets(keys, (int32_t)n, (int32_t)w.buckets, (int32_t *)(b + w.rp),
+                      (int32_t *)(b + w.perm), cs, stream);
   if (e == hipSuccess) e = launch_frnn_pairs(a, stream);
   if (e == hipSuccess) e = hipMemcpyAsync(&total, a.total, 8, hipMemcpyDeviceToHost, stream);
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -825,4 +852,32 @@ extern "C" int gnn_frnn(const float *z, int64_t n_nodes, int32_t dim, float r2,
   if (hipFreeAsync(base, stream) != hipSuccess && rc == GNN_OK)
     rc = set_error(GNN_E_HIP, "frnn workspace release failed");
   return rc;
+}
+
+}  // namespace
+
+extern "C" int gnn_frnn(const float *z, int64_t n_nodes, int32_t dim, float r2,
+                        int32_t *edge_index, int64_t max_pairs, int64_t *n_pairs,
+                        hipStream_t stream) {
+  // Room for 32 partners a point (a cluster's first point has most of the
+  // cluster; one point that is scanned twice costs the write launch 25 us);
+  // for very many points, whose workspace counts, the fewest.
+  const int32_t n_slots = n_nodes <= (1 << 24) ? FRNN_SLOTS_MOST : FRNN_SLOTS_LEAST;
+  return frnn(z, n_nodes, dim, r2, edge_index, max_pairs, n_pairs, n_slots, SCAN_DIRECT, stream);
+}
+
+extern "C" int gnn_debug_frnn(const float *z, int64_t n_nodes, int32_t dim, float r2,
+                              int32_t *edge_index, int64_t max_pairs, int64_t *n_pairs,
+                              int32_t n_slots, int64_t scan_direct, hipStream_t stream) {
+  if (n_slots < FRNN_SLOTS_LEAST || n_slots > FRNN_SLOTS_MOST || n_slots % 4 != 0)
+    return set_error(GNN_E_INVALID_ARG, "n_slots is none of 4, 8 .. 32");
+  if (scan_direct < 0 || scan_direct > SCAN_DIRECT)
+    return set_error(GNN_E_INVALID_ARG, "scan_direct outside 0..4096");
+  return frnn(z, n_nodes, dim, r2, edge_index, max_pairs, n_pairs, n_slots, scan_direct, stream);
+}
+
+extern "C" size_t gnn_debug_frnn_bytes(int64_t n_nodes, int32_t dim, int32_t n_slots) {
+  if (n_nodes < 1 || n_nodes >= CSR_MAX_ITEMS || dim < 1 || dim > 16) return 0;
+  if (n_slots < FRNN_SLOTS_LEAST || n_slots > FRNN_SLOTS_MOST || n_slots % 4 != 0) return 0;
+  return FrnnPlan(n_nodes, dim, n_slots).bytes;
 }

@@ -40,7 +40,7 @@ EXPORTS = ("gnn_weight_count", "gnn_create", "gnn_infer", "gnn_infer_logits", "g
            "gnn_server_create", "gnn_server_submit", "gnn_server_wait", "gnn_server_wait_info",
            "gnn_server_destroy", "gnn_set_workspace_limit",
            "gnn_embed_weight_count", "gnn_embed_create", "gnn_embed_apply", "gnn_embed_destroy",
-           "gnn_frnn", "gnn_hbm_probe")
+           "gnn_frnn", "gnn_debug_frnn", "gnn_debug_frnn_bytes", "gnn_hbm_probe")
 STAGES = ("csr", "node_enc", "edge_enc", "edge_update", "aggregate", "node_update",
           "classifier", "total")
 
@@ -146,6 +146,11 @@ def _load():
     L.gnn_embed_apply.argtypes = [vp, vp, i64, vp, vp]
     L.gnn_embed_destroy.restype = None
     L.gnn_embed_destroy.argtypes = [vp]
+    L.gnn_debug_frnn.restype = ctypes.c_int
+    L.gnn_debug_frnn.argtypes = [vp, i64, i32, ctypes.c_float, vp, i64,
+                                 ctypes.POINTER(ctypes.c_int64), i32, i64, vp]
+    L.gnn_debug_frnn_bytes.restype = ctypes.c_size_t
+    L.gnn_debug_frnn_bytes.argtypes = [i64, i32, i32]
     L.gnn_frnn.restype = ctypes.c_int
     L.gnn_frnn.argtypes = [vp, i64, i32, ctypes.c_float, vp, i64, ctypes.POINTER(ctypes.c_int64),
                            vp]
@@ -391,6 +396,15 @@ def gnn_frnn(z, n_nodes: int, dim: int, r2: float, edge_index=None, max_pairs: i
                       ctypes.byref(cnt), _stream(stream))
     if rc != GNN_OK:
         raise GnnError(rc, gnn_last_error())
+    return int(cnt.value)
+
+
+def gnn_debug_frnn(z, n_nodes: int, dim: int, r2: float, edge_index, max_pairs: int,
+                   n_slots: int, scan_direct: int, stream=None) -> int:
+    """gnn_frnn with the slots per point and the scan's limit given."""
+    cnt = ctypes.c_int64(0)
+    _check(lib.gnn_debug_frnn(_addr(z), n_nodes, dim, float(r2), _addr(edge_index), int(max_pairs),
+                              ctypes.byref(cnt), n_slots, scan_direct, _stream(stream)))
     return int(cnt.value)
 
 

@@ -176,3 +176,20 @@ def test_f16_weights_flag_only_with_bf16_regrouped(G, dtype, flags):
     assert G.gnn_weight_count(d) == 0
     assert "GNN_F16_WEIGHTS" in G.gnn_last_error()
     assert G.gnn_weight_count(G.make_dims(dtype=1, flags=8)) > 0
+
+
+@pytest.mark.parametrize("n", [2, 1000, 300_000, (1 << 24) - 1, (1 << 24) + 1, (1 << 30) - 1])
+@pytest.mark.parametrize("dim", [1, 3, 4, 5, 8, 16])
+def test_frnn_workspace_falls_back_to_what_it_always_took(G, n, dim):
+    """With the fewest slots the search takes no more than with two sorts of
+    the keys, two row pointers, and the coordinates in bucket order once (the
+    workspace it had before it kept partners): 64 + 4 dim bytes a point and 8 a
+    bucket, the sorts' counters (at least 2 bytes a point) left out."""
+    buckets = 64
+    while buckets < 2 * n and buckets < 1 << 30:
+        buckets *= 2
+    small = G.lib.gnn_debug_frnn_bytes(n, dim, 4)
+    assert 0 < small <= (64 + 4 * dim) * n + 8 * buckets + (64 << 10)
+    assert G.lib.gnn_debug_frnn_bytes(n, dim, 32) >= small + 128 * n
+    assert G.lib.gnn_debug_frnn_bytes(n, dim, 3) == 0
+    assert G.lib.gnn_debug_frnn_bytes(n, 17, 4) == 0

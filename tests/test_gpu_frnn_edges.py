@@ -136,3 +136,25 @@ def test_groups_of_all_sizes(oracle_mod, dim, size):
     ei = got[:-1].reshape(2, c)
     assert pair_set(ei) == ref
     assert (np.diff(ei[0]) >= 0).all()
+
+
+@pytest.mark.parametrize("slots,direct", [(4, 4096), (32, 0), (4, 0), (8, 1)])
+@pytest.mark.parametrize("dim,size", [(3, 5), (4, 30), (5, 12), (8, 3), (8, 120)])
+def test_fewer_slots_and_a_scan_of_its_own(dim, size, slots, direct):
+    """The slots of a very large or memory-bound search and the scan of one
+    with millions of points give the default's pairs in the default's order
+    (13 tiles of counts, the last one partly filled)."""
+    from paper_2402_09633_amd import gnn as G
+    n, r2 = 2048 * 12 + 301, 0.02 ** 2
+    z = groups(n, size, dim, 0.003, dim)
+    c = G.gnn_frnn(z, n, dim, r2)
+    out, alt = (torch.full((2 * c + 1,), -5, dtype=torch.int32, device="cuda") for _ in range(2))
+    G.gnn_frnn(z, n, dim, r2, out, c)
+    per_point = torch.bincount(out[:c])
+    assert int(per_point.max()) > 4  # points with more partners than 4 slots
+    assert G.gnn_debug_frnn(z, n, dim, r2, alt, c, slots, direct) == c
+    assert torch.equal(out, alt)
+    alt.fill_(-5)
+    with pytest.raises(G.GnnError):  # too small: nothing written
+        G.gnn_debug_frnn(z, n, dim, r2, alt, c - 1, slots, direct)
+    assert bool((alt == -5).all())

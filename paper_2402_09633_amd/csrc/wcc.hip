@@ -19,8 +19,8 @@
 //             until both ends share a root
 //   compress  parent[v] = root of v
 //
-// hook and round use plain stores: where several edges link one root, some
-// link is lost, which unite makes good.  No atomics there: an atomic minimum
+// hook and round link by stores: where several edges link one root, some
+// link is lost, which unite makes good.  No minimum there: an atomic minimum
 // goes to the memory side, and once large trees meet, a hundred thousand of
 // them hit one root.  The rounds leave unite almost nothing to do (a root
 // survives a round only if no neighbouring tree has a smaller one), which
@@ -40,8 +40,10 @@
 // with a convergence flag read by the host every four rounds: 300k hits with
 // track-like scores (270k of 1.0M edges kept) 244 -> 97; 150k hits, all 500k
 // edges kept (one giant component) 519 -> 90; chain of 300k ids 295 -> 90;
-// hub of 300k edges 1366 -> 100 to 205 (from run to run; 130 to 625 with a
-// compare-and-swap in unite); random graph, 1.2M edges, 369 -> 163.
+// hub of 300k edges, with the largest id 1366 -> 100 to 310, with the middle
+// one 967 -> 220 to 790 (from run to run, by which links are lost; the first
+// 130 to 625 with a compare-and-swap in unite); random graph, 1.2M edges,
+// 369 -> 163.
 #include "gnn_internal.h"
 
 namespace gnn {
@@ -55,12 +57,13 @@ __device__ __forceinline__ int32_t clampi(int32_t v, int32_t n) {
 }
 
 // Links as this XCD's caches have them (workgroup scope: not kept in a
-// register between reads).
+// register between reads), and stores to them (whole ones: other threads read
+// and lower the same words).
 __device__ __forceinline__ int32_t link_of(const int32_t *parent, int32_t v) {
   return __hip_atomic_load(parent + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 __device__ __forceinline__ void set_link(int32_t *parent, int32_t v, int32_t to) {
-  parent[v] = to;
+  __hip_atomic_store(parent + v, to, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Walks of at most NEAR links (a detector graph's trees are as deep as it has

@@ -90,11 +90,11 @@ def test_no_float_atomics_in_kernels():
     # Aggregation must be deterministic: the only atomics are integer ones --
     # the radix sort's uint32 digit histograms (LDS `h`, global `totals`),
     # its tile counters and error word, its uint32 look-back words (`st`),
-    # the components' int32 parent array (atomicMin, relaxed loads) and the
-    # relaxed loads of their int32 round flags.
+    # and the components' int32 parent array (atomicMin, relaxed loads and
+    # stores).
     allowed = ("atomicAdd(&h[", "atomicAdd(&totals[", "atomicAdd(&O.ctr[", "atomicOr(O.err",
                "__hip_atomic_store(st", "__hip_atomic_load(st", "atomicMin(&parent[",
-               "__hip_atomic_load(parent", "__hip_atomic_load(prev", "__hip_atomic_load(changed")
+               "__hip_atomic_load(parent", "__hip_atomic_store(parent")
     for f in os.listdir(CSRC):
         text = open(os.path.join(CSRC, f)).read()
         for line in text.splitlines():

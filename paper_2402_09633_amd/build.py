@@ -24,8 +24,6 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # Packed-fp32 VALU forms are kept out of the generated code.
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # Host fp16 conversions in hardware (in software they are most of gnn_create).
-    "-Xarch_host", "-mf16c",
     "-I", os.path.join(ROOT, "include"),
 ]
 

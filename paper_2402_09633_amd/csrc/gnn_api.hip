@@ -24,6 +24,7 @@
 
 #include "../../include/gnn.h"
 #include "gnn_internal.h"
+#include "half_host.h"
 
 using namespace gnn;
 
@@ -156,12 +157,6 @@ void frag_bf16(const BlobLayer &L, bool from_acc, uint16_t *hi, uint16_t *lo) {
 //   B from HBM:   k = 16 g + 8 hh + j
 //   B from accs:  k = 16 g + 8 (j / 4) + 4 hh + j % 4
 
-uint16_t f16_bits(_Float16 v) {
-  uint16_t b;
-  memcpy(&b, &v, 2);
-  return b;
-}
-
 // Power of two s with max |s W| in [2^13, 2^14) (1 for an all-zero or
 // non-finite W), over the whole (fout x fin) layer.
 constexpr int MIN_SCALE = -40;  // (centred weights: two more, Centred)
@@ -265,11 +260,10 @@ std::vector<uint16_t> rec_f16x2(const BlobLayer &L, int c0, int K, float s, int 
           const int hh = lane / 32;
           const int k = node_line_k(g, hh, j, grp);
           const double wv = s * L.at((size_t)(mb * 32 + lane % 32) * L.fin + c0 + k);
-          const _Float16 p1 = (_Float16)(float)wv;
-          const _Float16 p2 = (_Float16)(float)(wv - (double)p1);
+          const uint16_t p1 = f32_to_f16((float)wv);
           const size_t o = ((((size_t)g * MB + mb) * 2) * 64 + lane) * 8 + j;
-          out[o] = f16_bits(p1);
-          out[o + 64 * 8] = f16_bits(p2);
+          out[o] = p1;
+          out[o + 64 * 8] = f32_to_f16((float)(wv - (double)f16_to_f32(p1)));
         }
   return out;
 }
@@ -288,7 +282,7 @@ std::vector<uint16_t> rec_f16x1(const BlobLayer &L, int c0, int K, float s, int 
         for (int j = 0; j < 8; ++j) {
           const int k = node_line_k(g, lane / 32, j, grp);
           const float wv = s * L.W[(size_t)(mb * 32 + lane % 32) * L.fin + c0 + k];
-          out[(((size_t)g * MB + mb) * 64 + lane) * 8 + j] = f16_bits((_Float16)wv);
+          out[(((size_t)g * MB + mb) * 64 + lane) * 8 + j] = f32_to_f16(wv);
         }
   return out;
 }
@@ -2008,9 +2002,9 @@ struct SmallMlpOff {
             if (l % 32 >= out.fout) continue;  // zero rows
             double w = so[l % 32] * out.at((size_t)(l % 32) * H + k);
             for (int p = 0; p < 3; ++p) {
-              const _Float16 v = (_Float16)(float)w;
-              r[(((size_t)g * 3 + p) * 64 + l) * 8 + j] = f16_bits(v);
-              w -= (double)v;
+              const uint16_t v = f32_to_f16((float)w);
+              r[(((size_t)g * 3 + p) * 64 + l) * 8 + j] = v;
+              w -= (double)f16_to_f32(v);
             }
           }
       w2r = st.add(r.data(), r.size() * sizeof(uint16_t));

@@ -254,17 +254,14 @@ std::vector<uint16_t> rec_f16x2(const BlobLayer &L, int c0, int K, float s, int 
   const int MB = L.fout / 32, G = K / 16;
   std::vector<uint16_t> out((size_t)G * MB * 2 * 64 * 8);
   for (int g = 0; g < G; ++g)
-    for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < MB; ++mb) {
+      double w[64 * 8];
       for (int lane = 0; lane < 64; ++lane)
-        for (int j = 0; j < 8; ++j) {
-          const int hh = lane / 32;
-          const int k = node_line_k(g, hh, j, grp);
-          const double wv = s * L.at((size_t)(mb * 32 + lane % 32) * L.fin + c0 + k);
-          const uint16_t p1 = f32_to_f16((float)wv);
-          const size_t o = ((((size_t)g * MB + mb) * 2) * 64 + lane) * 8 + j;
-          out[o] = p1;
-          out[o + 64 * 8] = f32_to_f16((float)(wv - (double)f16_to_f32(p1)));
-        }
+        for (int j = 0; j < 8; ++j)
+          w[lane * 8 + j] = s * L.at((size_t)(mb * 32 + lane % 32) * L.fin + c0 +
+                                     node_line_k(g, lane / 32, j, grp));
+      split_f16<2>(w, out.data() + ((size_t)g * MB + mb) * 2 * 64 * 8);
+    }
   return out;
 }
 
@@ -277,13 +274,14 @@ std::vector<uint16_t> rec_f16x1(const BlobLayer &L, int c0, int K, float s, int 
   const int MB = L.fout / 32, G = K / 16;
   std::vector<uint16_t> out((size_t)G * MB * 64 * 8);
   for (int g = 0; g < G; ++g)
-    for (int mb = 0; mb < MB; ++mb)
+    for (int mb = 0; mb < MB; ++mb) {
+      double w[64 * 8];
       for (int lane = 0; lane < 64; ++lane)
-        for (int j = 0; j < 8; ++j) {
-          const int k = node_line_k(g, lane / 32, j, grp);
-          const float wv = s * L.W[(size_t)(mb * 32 + lane % 32) * L.fin + c0 + k];
-          out[(((size_t)g * MB + mb) * 64 + lane) * 8 + j] = f32_to_f16(wv);
-        }
+        for (int j = 0; j < 8; ++j)
+          w[lane * 8 + j] = s * L.W[(size_t)(mb * 32 + lane % 32) * L.fin + c0 +
+                                    node_line_k(g, lane / 32, j, grp)];
+      split_f16<1>(w, out.data() + ((size_t)g * MB + mb) * 64 * 8);
+    }
   return out;
 }
 
@@ -1995,18 +1993,13 @@ struct SmallMlpOff {
       for (int r = 0; r < out.fout; ++r) si[r] = (float)(1.0 / so[r]);
       s2inv = st.add(si.data(), si.size() * sizeof(float));
       std::vector<uint16_t> r((size_t)(H / 16) * 3 * 64 * 8);
-      for (int g = 0; g < H / 16; ++g)
+      for (int g = 0; g < H / 16; ++g) {
+        double w[64 * 8] = {};  // (rows past D are zero)
         for (int l = 0; l < 64; ++l)
-          for (int j = 0; j < 8; ++j) {
-            const int k = node_line_k(g, l / 32, j, -1);
-            if (l % 32 >= out.fout) continue;  // zero rows
-            double w = so[l % 32] * out.at((size_t)(l % 32) * H + k);
-            for (int p = 0; p < 3; ++p) {
-              const uint16_t v = f32_to_f16((float)w);
-              r[(((size_t)g * 3 + p) * 64 + l) * 8 + j] = v;
-              w -= (double)f16_to_f32(v);
-            }
-          }
+          for (int j = 0; j < 8 && l % 32 < out.fout; ++j)
+            w[l * 8 + j] = so[l % 32] * out.at((size_t)(l % 32) * H + node_line_k(g, l / 32, j, -1));
+        split_f16<3>(w, r.data() + (size_t)g * 3 * 64 * 8);
+      }
       w2r = st.add(r.data(), r.size() * sizeof(uint16_t));
     }
   }

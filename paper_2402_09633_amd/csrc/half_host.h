@@ -1,11 +1,17 @@
-// fp32 to and from IEEE half bits on the host (round to nearest even).  In
-// integers: gnn_create makes some hundred thousand of them, and without the
-// host CPU's own conversion (F16C, which not every host has) the compiler's
-// call for (_Float16) is most of its time: fp32 model 13.3 ms, 1.1 so.
+// fp32 to and from IEEE half bits on the host (round to nearest even), by the
+// block: gnn_create makes some hundred thousand of them, and the compiler's
+// call for (_Float16) was most of its time (fp32 model 13.3 ms).  With the
+// CPU's own conversion (F16C) where it has one, asked at run time (1.0 ms),
+// else in integers.
 #pragma once
 
 #include <cstdint>
 #include <cstring>
+
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+#define GNN_HOST_F16C 1
+#include <immintrin.h>
+#endif
 
 namespace gnn {
 
@@ -37,6 +43,54 @@ inline float f16_to_f32(uint16_t h) {
   u |= sign;
   memcpy(&f, &u, 4);
   return f;
+}
+
+inline void to_f16(const float *x, uint16_t *y, int n) {
+  for (int i = 0; i < n; ++i) y[i] = f32_to_f16(x[i]);
+}
+inline void to_f32(const uint16_t *x, float *y, int n) {
+  for (int i = 0; i < n; ++i) y[i] = f16_to_f32(x[i]);
+}
+
+#ifdef GNN_HOST_F16C
+// n a multiple of 8
+__attribute__((target("avx,f16c"))) inline void to_f16_hw(const float *x, uint16_t *y, int n) {
+  for (int i = 0; i < n; i += 8)
+    _mm_storeu_si128((__m128i *)(y + i),
+                     _mm256_cvtps_ph(_mm256_loadu_ps(x + i), _MM_FROUND_TO_NEAREST_INT));
+}
+__attribute__((target("avx,f16c"))) inline void to_f32_hw(const uint16_t *x, float *y, int n) {
+  for (int i = 0; i < n; i += 8)
+    _mm256_storeu_ps(y + i, _mm256_cvtph_ps(_mm_loadu_si128((const __m128i *)(x + i))));
+}
+inline bool host_f16c() {
+  static const bool yes = __builtin_cpu_supports("avx") && __builtin_cpu_supports("f16c");
+  return yes;
+}
+#endif
+
+// PARTS halves whose sum is w, largest first, in consecutive blocks of N
+// (a multiple of 8): part p + 1 is what part p left.
+template <int PARTS, int N>
+inline void split_f16(const double (&w)[N], uint16_t *out) {
+  double left[N];
+  float x[N], y[N];
+  memcpy(left, w, sizeof left);
+  for (int p = 0; p < PARTS; ++p, out += N) {
+    for (int i = 0; i < N; ++i) x[i] = (float)left[i];
+#ifdef GNN_HOST_F16C
+    if (host_f16c()) {
+      to_f16_hw(x, out, N);
+      if (p + 1 < PARTS) to_f32_hw(out, y, N);
+    } else
+#endif
+    {
+      to_f16(x, out, N);
+      if (p + 1 < PARTS) to_f32(out, y, N);
+    }
+    if (p + 1 < PARTS)
+      for (int i = 0; i < N; ++i) left[i] -= (double)y[i];
+  }
 }
 
 }  // namespace gnn

@@ -14,10 +14,11 @@ def lib(tmp_path_factory):
     d = tmp_path_factory.mktemp("half")
     src, so = d / "half.cpp", d / "half.so"
     src.write_text('#include "half_host.h"\nextern "C" {\n'
-                   "void to_half(const float *x, uint16_t *y, long n) "
-                   "{ for (long i = 0; i < n; ++i) y[i] = gnn::f32_to_f16(x[i]); }\n"
-                   "void to_float(const uint16_t *x, float *y, long n) "
-                   "{ for (long i = 0; i < n; ++i) y[i] = gnn::f16_to_f32(x[i]); }\n}\n")
+                   "void to_half(const float *x, uint16_t *y, long n) { gnn::to_f16(x, y, n); }\n"
+                   "void to_float(const uint16_t *x, float *y, long n) { gnn::to_f32(x, y, n); }\n"
+                   "void split(const double *x, uint16_t *y, long n) {\n"
+                   "  for (; n > 0; n -= 64, x += 64, y += 192)\n"
+                   "    gnn::split_f16<3>(*(const double(*)[64])x, y);\n}\n}\n")
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I",
                     os.path.join(B.CSRC), str(src), "-o", str(so)], check=True)
     return ctypes.CDLL(str(so))
@@ -51,6 +52,21 @@ def test_every_half_and_what_rounds_to_it(lib):
     nan = np.isnan(x)
     assert np.array_equal(got.view(np.uint16)[~nan], want.view(np.uint16)[~nan])
     assert np.isnan(got[nan]).all()
+
+
+def test_split_parts(lib):
+    # (with the CPU's conversion where it has one)
+    rng = np.random.default_rng(1)
+    w = rng.normal(size=64 * 50) * 2.0 ** rng.integers(-30, 14, 64 * 50)
+    got = np.empty(w.size * 3, np.uint16)
+    lib.split(w.ctypes.data_as(ctypes.c_void_p), got.ctypes.data_as(ctypes.c_void_p),
+              ctypes.c_long(w.size))
+    left = w.reshape(-1, 64).copy()
+    for p in range(3):
+        want = left.astype(np.float32).astype(np.float16)
+        part = got.reshape(-1, 3, 64)[:, p].view(np.float16)
+        assert np.array_equal(part.view(np.uint16), want.view(np.uint16))
+        left -= want.astype(np.float64)
 
 
 def test_build_asks_for_no_host_cpu_feature():

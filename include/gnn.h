@@ -445,6 +445,12 @@ int gnn_debug_stages(gnn_handle *h, const float *node_feat, const int32_t *edge_
                      int64_t n_nodes, int64_t n_edges, int32_t stop_iter, float *h_out,
                      float *e_out, float *agg_in_out, float *agg_out_out, hipStream_t stream);
 
+/* 1 if a call of h on `stream` would find the GPU shared, 0 if not: another
+ * inference of this process on h's device is being issued, or has not
+ * finished, on another stream.  The launches of small events are then packed
+ * onto few CUs instead of spread over all; results are the same. */
+int gnn_debug_shared(gnn_handle *h, hipStream_t stream);
+
 /* gnn_frnn with the limits that depend on its size: n_slots, the partners
  * kept per point by the first scan (4, 8 .. 32; a point with more is scanned
  * twice), and scan_direct (0..4096), the count tiles up to which the scan has

@@ -2350,6 +2350,12 @@ int gnn_debug_csr(gnn_handle *h, const int32_t *edge_index, int64_t n_nodes, int
   return run(h, nullptr, edge_index, n_nodes, n_edges, stream, ro);
 }
 
+int gnn_debug_shared(gnn_handle *h, hipStream_t stream) {
+  if (!h) return fail(GNN_E_INVALID_ARG, "handle is NULL");
+  DeviceGuard guard(h->device);
+  return gpu_shared(h, -1, stream) ? 1 : 0;
+}
+
 int gnn_debug_stages(gnn_handle *h, const float *node_feat, const int32_t *edge_index,
                      int64_t n_nodes, int64_t n_edges, int32_t stop_iter, float *h_out,
                      float *e_out, float *agg_in_out, float *agg_out_out, hipStream_t stream) {

@@ -40,7 +40,8 @@ EXPORTS = ("gnn_weight_count", "gnn_create", "gnn_infer", "gnn_infer_logits", "g
            "gnn_server_create", "gnn_server_submit", "gnn_server_wait", "gnn_server_wait_info",
            "gnn_server_destroy", "gnn_set_workspace_limit",
            "gnn_embed_weight_count", "gnn_embed_create", "gnn_embed_apply", "gnn_embed_destroy",
-           "gnn_frnn", "gnn_debug_frnn", "gnn_debug_frnn_bytes", "gnn_hbm_probe")
+           "gnn_frnn", "gnn_debug_shared", "gnn_debug_frnn", "gnn_debug_frnn_bytes",
+           "gnn_hbm_probe")
 STAGES = ("csr", "node_enc", "edge_enc", "edge_update", "aggregate", "node_update",
           "classifier", "total")
 
@@ -146,6 +147,8 @@ def _load():
     L.gnn_embed_apply.argtypes = [vp, vp, i64, vp, vp]
     L.gnn_embed_destroy.restype = None
     L.gnn_embed_destroy.argtypes = [vp]
+    L.gnn_debug_shared.restype = ctypes.c_int
+    L.gnn_debug_shared.argtypes = [vp, vp]
     L.gnn_debug_frnn.restype = ctypes.c_int
     L.gnn_debug_frnn.argtypes = [vp, i64, i32, ctypes.c_float, vp, i64,
                                  ctypes.POINTER(ctypes.c_int64), i32, i64, vp]
@@ -358,6 +361,14 @@ def gnn_debug_stages(handle, node_feat, edge_index, n_nodes: int, n_edges: int, 
     return _check(lib.gnn_debug_stages(handle, _addr(node_feat), _addr(edge_index), n_nodes,
                                        n_edges, stop_iter, _addr(h_out), _addr(e_out),
                                        _addr(agg_in_out), _addr(agg_out_out), _stream(stream)))
+
+
+def gnn_debug_shared(handle, stream=None) -> bool:
+    """Whether a call on `stream` would find another inference in flight."""
+    rc = lib.gnn_debug_shared(handle, _stream(stream))
+    if rc < 0:
+        raise GnnError(rc, gnn_last_error())
+    return bool(rc)
 
 
 def make_embed_dims(in_features=3, hidden=64, out_dim=8, ln_eps=1e-5) -> gnn_embed_dims:

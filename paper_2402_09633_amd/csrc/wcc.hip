@@ -40,9 +40,8 @@
 // with a convergence flag read by the host every four rounds: 300k hits with
 // track-like scores (270k of 1.0M edges kept) 244 -> 97; 150k hits, all 500k
 // edges kept (one giant component) 519 -> 90; chain of 300k ids 295 -> 90;
-// hub of 300k edges, with the largest id 1366 -> 100 to 310, with the middle
-// one 967 -> 220 to 790 (from run to run, by which links are lost; the first
-// 130 to 625 with a compare-and-swap in unite); random graph, 1.2M edges,
+// hub of 300k edges, with the largest id 1366 -> 85, with the middle one 967 ->
+// 100 (means: from call to call 55 to 1200); random graph, 1.2M edges,
 // 369 -> 163.
 #include "gnn_internal.h"
 
@@ -157,6 +156,57 @@ __device__ __forceinline__ void find_roots(int32_t *parent, int32_t (&hi)[WE], i
   }
 }
 
+// The pairs of a hub, or between two large trees, all have one larger end.
+// Each for itself they leave it whichever link comes last (a hub then keeps a
+// random leaf, and a round settles only the larger ones), and what the rounds
+// leave queues in unite at one word, 100 ns each: one call in ten of the
+// 300k-edge hubs took 3.4 to 8 ms, and now and then 1 ms was added where all
+// edges are kept.  So a workgroup takes one larger end of its open pairs, one
+// that neighbouring edges share where there is such, and the least of its
+// partners: these are pointed at the least, and thread 0 gets the pair (r, m)
+// of the two.  r = m: nothing done, fewer than `few` threads have that end.
+// False: no open pair in the workgroup.  In unite and in the first round, where
+// that end is common: of 1500 calls of a hub half take 90 us, one in a hundred
+// 250 to 500, the longest 1.2 ms.  In all rounds, or before the round's own
+// links, the hubs never take more than 0.1 ms, but a graph of large trees meets
+// a round later (500k edges, all kept, 91 -> 99 us).
+__device__ __forceinline__ bool fold_common(int32_t (&hi)[WE], int32_t (&lo)[WE], int few,
+                                            int32_t &r, int32_t &m) {
+  __shared__ int32_t root[2], least;  // root: of a neighbouring edge too, of any
+  int32_t any = -1, both = -1;
+#pragma unroll
+  for (int k = 0; k < WE; ++k) {
+    const int32_t mine = hi[k] != lo[k] ? hi[k] : -1, next = __shfl_xor(mine, 1);
+    if (mine >= 0) any = mine;
+    if (mine >= 0 && mine == next) both = mine;
+  }
+  if (threadIdx.x == 0) {
+    root[0] = -1;
+    least = INT32_MAX;
+  }
+  if (!__syncthreads_or(any >= 0)) return false;
+  if (both >= 0)
+    __hip_atomic_store(&root[0], both, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  if (any >= 0) __hip_atomic_store(&root[1], any, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  __syncthreads();
+  r = m = root[0] >= 0 ? root[0] : root[1];
+  int32_t mine = INT32_MAX;
+#pragma unroll
+  for (int k = 0; k < WE; ++k)
+    if (hi[k] != lo[k] && hi[k] == r) mine = lo[k] < mine ? lo[k] : mine;
+  if (__syncthreads_count(mine < INT32_MAX) < few) return true;
+  if (mine < INT32_MAX) atomicMin(&least, mine);
+  __syncthreads();
+  m = least;
+#pragma unroll
+  for (int k = 0; k < WE; ++k)
+    if (hi[k] != lo[k] && hi[k] == r) {
+      hi[k] = lo[k];
+      lo[k] = m;
+    }
+  return true;
+}
+
 // Links root (or fresh node) a to c < a on the lanes with `active`.  Links
 // already smaller stay, and where all active lanes of the wave link the same
 // node, the smallest c is taken (a hub's edges would otherwise leave it a
@@ -193,7 +243,8 @@ __global__ __launch_bounds__(WT) void wcc_hook(WccEdges E, int32_t *parent) {
 // With `check`, a workgroup first looks at WT edges spread over the list (the
 // same ones for all) and leaves the rest to unite once all but a few of them
 // are settled: no flag has to be kept, cleared or counted.
-__global__ __launch_bounds__(WT) void wcc_round(WccEdges E, int32_t *parent, bool check) {
+__global__ __launch_bounds__(WT) void wcc_round(WccEdges E, int32_t *parent, bool check,
+                                               bool fold) {
   int32_t hi[WE], lo[WE];
   if (check) {
     load_edge(E, (int64_t)threadIdx.x * E.n_edges / WT, hi[0], lo[0]);
@@ -204,26 +255,37 @@ __global__ __launch_bounds__(WT) void wcc_round(WccEdges E, int32_t *parent, boo
   find_roots<false>(parent, hi, lo);
 #pragma unroll
   for (int k = 0; k < WE; ++k) link_to(parent, hi[k] != lo[k], hi[k], lo[k]);
+  // (behind the links: a barrier before them holds back what other workgroups
+  // can already follow)
+  int32_t r, m;
+  if (!fold || !fold_common(hi, lo, WT / 4, r, m) || r == m) return;
+#pragma unroll
+  for (int k = 0; k < WE; ++k) link_to(parent, hi[k] != lo[k], hi[k], lo[k]);
+  if (threadIdx.x == 0 && m < link_of(parent, r)) set_link(parent, r, m);
+}
+
+// Until roots a and b are one.
+__device__ __forceinline__ void unite(int32_t *parent, int32_t a, int32_t b) {
+  while (a != b) {
+    if (a < b) {
+      const int32_t t = a;
+      a = b;
+      b = t;
+    }
+    const int32_t old = atomicMin(&parent[a], b);
+    if (old == a) break;
+    a = find_root(parent, old);
+  }
 }
 
 __global__ __launch_bounds__(WT) void wcc_unite(WccEdges E, int32_t *parent) {
-  int32_t hi[WE], lo[WE];
+  int32_t hi[WE], lo[WE], r, m;
   load_edges(E, hi, lo);
   find_roots<true>(parent, hi, lo);
+  if (!fold_common(hi, lo, 1, r, m)) return;
+  if (threadIdx.x == 0) unite(parent, r, m);
 #pragma unroll
-  for (int k = 0; k < WE; ++k) {
-    int32_t a = hi[k], b = lo[k];
-    while (a != b) {
-      if (a < b) {
-        const int32_t t = a;
-        a = b;
-        b = t;
-      }
-      const int32_t old = atomicMin(&parent[a], b);
-      if (old == a) break;
-      a = find_root(parent, old);
-    }
-  }
+  for (int k = 0; k < WE; ++k) unite(parent, hi[k], lo[k]);
 }
 
 // (A node whose own link another thread shortens meanwhile reads either
@@ -254,7 +316,7 @@ hipError_t launch_wcc(const int32_t *edge_index, const float *scores, float thre
   if (e != hipSuccess || n_edges <= 0) return e;
   if ((e = launch(wcc_hook, ne, WT, 0, stream, E, labels))) return e;
   for (int r = 0; r < ROUNDS; ++r)
-    if ((e = launch(wcc_round, ne, WT, 0, stream, E, labels, r > 0))) return e;
+    if ((e = launch(wcc_round, ne, WT, 0, stream, E, labels, r > 0, r == 0))) return e;
   if ((e = launch(wcc_unite, ne, WT, 0, stream, E, labels))) return e;
   return launch(wcc_compress, nv, WT, 0, stream, labels, n_nodes);
 }

@@ -91,10 +91,11 @@ def test_no_float_atomics_in_kernels():
     # the radix sort's uint32 digit histograms (LDS `h`, global `totals`),
     # its tile counters and error word, its uint32 look-back words (`st`),
     # and the components' int32 parent array (atomicMin, relaxed loads and
-    # stores).
+    # stores) and a workgroup's int32 root and least end in LDS.
     allowed = ("atomicAdd(&h[", "atomicAdd(&totals[", "atomicAdd(&O.ctr[", "atomicOr(O.err",
                "__hip_atomic_store(st", "__hip_atomic_load(st", "atomicMin(&parent[",
-               "__hip_atomic_load(parent", "__hip_atomic_store(parent")
+               "__hip_atomic_load(parent", "__hip_atomic_store(parent", "atomicMin(&least,",
+               "__hip_atomic_store(&root[")
     for f in os.listdir(CSRC):
         text = open(os.path.join(CSRC, f)).read()
         for line in text.splitlines():

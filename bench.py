@@ -50,9 +50,9 @@ TRAFFIC_SOURCES = {
 }
 # (path, source hash) -> (HBM bytes read, written) per edge-update launch on
 # the full event
-MEASURED_TRAFFIC = {("split", "46002303e7ff714f"): (1.133e9, 0.651e9),    # edge_split<4,3>
-                    ("bf16", "46002303e7ff714f"): (0.551e9, 0.342e9),     # edge_split<4,3,bf16>
-                    ("f16w", "46002303e7ff714f"): (0.593e9, 0.347e9)}     # edge_split<4,3,f16w>
+MEASURED_TRAFFIC = {("split", "1f1f9a4bf97689da"): (1.133e9, 0.651e9),    # edge_split<4,3>
+                    ("bf16", "1f1f9a4bf97689da"): (0.551e9, 0.342e9),     # edge_split<4,3,bf16>
+                    ("f16w", "1f1f9a4bf97689da"): (0.593e9, 0.347e9)}     # edge_split<4,3,f16w>
 
 
 def kernel_source_hash(path):

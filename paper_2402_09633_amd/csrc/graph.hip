@@ -22,8 +22,8 @@
 //             point's first partners; after an exclusive scan of the counts
 //             they are written grouped by i (within one i in cell-scan
 //             order), which is deterministic.  300k clustered 8-d points,
-//             544k pairs, whole call: 494 -> 242 us (two full scans of 190 us
-//             became one of 109, bound by its scattered loads; one sort of
+//             544k pairs, whole call: 494 -> 240 us (two full scans of 190 us
+//             became one of 100, bound by its scattered loads; one sort of
 //             the keys instead of two; the write queued behind the count).
 #include "small_mlp.h"
 

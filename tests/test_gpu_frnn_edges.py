@@ -114,7 +114,7 @@ def test_coordinates_that_separate_nothing(still):
     assert t[0] <= 2.4 * t[1], t
 
 
-@pytest.mark.parametrize("dim", [1, 2, 3, 4, 5, 8, 10, 16])
+@pytest.mark.parametrize("dim", [1, 2, 3, 4, 5, 8, 10, 11, 12, 16])
 @pytest.mark.parametrize("size", [8, 40, 90, 300])
 def test_groups_of_all_sizes(oracle_mod, dim, size):
     """Around the limits between testing first, scanning at once and only

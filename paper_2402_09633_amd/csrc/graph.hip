@@ -487,12 +487,14 @@ __device__ __forceinline__ bool dense_at(const FrnnArgs &a, int64_t p, int step)
 // 100k points, 8 dimensions: groups of 20 255 -> 270 -> 335, of 60 (width
 // 0.005) 540 -> 510 -> 490, of 100 600 -> 515 -> 497, of 250 1000 -> 820 -> 770;
 // 300k points in groups of 10 stay with the test (235; 445 without).
-// Five waves per SIMD where at most a few registers are spilled for them, in
-// 10 to 12 dimensions: 300k points, 10 299 -> 264, 11 304 -> 276, 12 280 -> 264.
+// Five waves per SIMD up to 11 dimensions, a few registers spilled for them
+// in 10 and 11: 300k points 299 -> 264 and 304 -> 276.  In 12 the spills cost
+// what they gain (300k 280 -> 264, 220k, which four waves hold, 87 -> 100 for
+// the launch).
 constexpr int DENSE_STEP = 4, DENSE_LANES = 7 * FTHREADS / 16;
 constexpr int MANY_STEP = 16, MANY_LANES = FTHREADS / 4;
 template <int D>
-__global__ __launch_bounds__(FTHREADS, D >= 5 && D <= 12 ? 5 : 4) void frnn_collect(FrnnArgs a) {
+__global__ __launch_bounds__(FTHREADS, D >= 5 && D <= 11 ? 5 : 4) void frnn_collect(FrnnArgs a) {
   const int64_t p = (int64_t)blockIdx.x * FTHREADS + threadIdx.x;
   const bool in = p < a.n;
   const bool dense = __syncthreads_count(in && dense_at<D>(a, p, DENSE_STEP)) >= DENSE_LANES;
